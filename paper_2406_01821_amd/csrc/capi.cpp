@@ -26,25 +26,24 @@ namespace {
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 struct DatasetMem {
-  int64_t n_pad_max, n_tiles_max, n_blocks;
-  size_t x_off, y_off, perm_off, tile_off, tau_off, counts_off, base_off, flags_off, tpart_off, total;
+  int64_t n_pad_max, n_tiles_max;
+  size_t x_off, y_off, perm_off, tile_off, tau_off, counts_off, head_off, part_off, total;
 };
 
 DatasetMem dataset_mem(int64_t n, int32_t nf, int32_t nc) {
   DatasetMem m{};
   m.n_pad_max = n > 0 ? ((n + AERL_TILE - 1) / AERL_TILE + nc) * AERL_TILE : 0;
   m.n_tiles_max = m.n_pad_max / AERL_TILE;
-  m.n_blocks = (n + kUploadBlock - 1) / kUploadBlock;
+  const UploadShape up = upload_shape(n, nf);
   size_t off = 0;
   m.x_off = off;     off = align256(off + sizeof(float) * (size_t)nf * (size_t)m.n_pad_max);
   m.y_off = off;     off = align256(off + sizeof(int32_t) * (size_t)m.n_pad_max);
   m.perm_off = off;  off = align256(off + sizeof(int32_t) * (size_t)m.n_pad_max);
   m.tile_off = off;  off = align256(off + sizeof(int32_t) * (size_t)(m.n_tiles_max + 1));
   m.tau_off = off;   off = align256(off + sizeof(float) * 2 * (size_t)nf);  // tau, 1/tau
-  m.counts_off = off; off = align256(off + sizeof(int32_t) * (size_t)(m.n_blocks * nc + 1));
-  m.base_off = off;  off = align256(off + sizeof(int32_t) * (size_t)(m.n_blocks * nc + 1));
-  m.flags_off = off; off = align256(off + sizeof(int32_t) * 2);
-  m.tpart_off = off; off = align256(off + sizeof(double) * 2 * (size_t)nf * kTauParts);
+  m.counts_off = off; off = align256(off + sizeof(int32_t) * (size_t)up.n_groups * (size_t)(nc + 1));
+  m.head_off = off;  off = align256(off + sizeof(int32_t) * (size_t)(nc + 2));
+  m.part_off = off;  off = align256(off + sizeof(double) * 3 * (size_t)nf * (size_t)up.parts);
   m.total = off;
   return m;
 }
@@ -75,12 +74,6 @@ void set_regions(DatasetRec &d, const int64_t *counts) {
   d.n_tiles = tile;
   d.n_pad = tile * AERL_TILE;
 }
-
-// RAII pinned host buffer.
-struct Pinned {
-  void *p = nullptr;
-  ~Pinned() { if (p) (void)hipHostFree(p); }
-};
 
 // Launch configuration of the plain hard-eval path.  Large set chunks (up to
 // 2048 rule sets per block) over single tiles: every staged tile serves many
@@ -254,6 +247,7 @@ void aerl_destroy(aerl_ctx *ctx) {
     if (kv.second.staging) (void)hipHostFree(kv.second.staging);
   }
   for (const auto &b : ctx->staging_pool) (void)hipHostFree(b.first);
+  if (ctx->upload_head) (void)hipHostFree(ctx->upload_head);
   delete ctx;
 }
 
@@ -299,56 +293,34 @@ aerl_status aerl_upload_dataset(aerl_ctx *ctx, const float *x, const int32_t *y,
   d.tile_info = reinterpret_cast<int32_t *>(base + M.tile_off);
   d.tau = reinterpret_cast<float *>(base + M.tau_off);
   d.inv_tau = d.tau + nf;
-  int32_t *counts_dev = reinterpret_cast<int32_t *>(base + M.counts_off);
-  int32_t *base_dev = reinterpret_cast<int32_t *>(base + M.base_off);
-  int32_t *flags_dev = reinterpret_cast<int32_t *>(base + M.flags_off);
-
-  const size_t nbc = (size_t)M.n_blocks * nc;
-  Pinned hbuf;
-  const size_t hbytes = sizeof(int32_t) * (2 * nbc + 2 + (size_t)M.n_tiles_max + 1);
-  AERL_HIP(ctx, hipHostMalloc(&hbuf.p, hbytes, hipHostMallocDefault));
-  int32_t *h_counts = static_cast<int32_t *>(hbuf.p);
-  int32_t *h_base = h_counts + nbc;
-  int32_t *h_flags = h_base + nbc;
-  int32_t *h_tiles = h_flags + 2;
-
-  AERL_HIP(ctx, launch_fill_i32(flags_dev, 2, 0, stream));
-  AERL_HIP(ctx, launch_validate_count(x, y, n, nf, nc, counts_dev, flags_dev, M.n_blocks, stream));
-  if (nbc) AERL_HIP(ctx, hipMemcpyAsync(h_counts, counts_dev, nbc * 4, hipMemcpyDeviceToHost, stream));
-  AERL_HIP(ctx, hipMemcpyAsync(h_flags, flags_dev, 8, hipMemcpyDeviceToHost, stream));
+  if (!ctx->upload_head)
+    AERL_HIP(ctx, hipHostMalloc(reinterpret_cast<void **>(&ctx->upload_head),
+                                sizeof(int32_t) * (AERL_MAX_CLASSES + 2), hipHostMallocDefault));
+  UploadLaunch u{};
+  u.x = x;
+  u.y = y;
+  u.n = n;
+  u.nf = nf;
+  u.nc = nc;
+  u.counts = reinterpret_cast<int32_t *>(base + M.counts_off);
+  u.head = reinterpret_cast<int32_t *>(base + M.head_off);
+  u.part = reinterpret_cast<double *>(base + M.part_off);
+  u.x_fm = d.x_fm;
+  u.y_pad = d.y_pad;
+  u.perm = d.perm;
+  u.tile_info = d.tile_info;
+  u.tau = d.tau;
+  AERL_HIP(ctx, launch_upload(u, stream));
+  AERL_HIP(ctx, hipMemcpyAsync(ctx->upload_head, u.head, sizeof(int32_t) * (size_t)(nc + 2),
+                               hipMemcpyDeviceToHost, stream));
   AERL_HIP(ctx, hipStreamSynchronize(stream));
-  if (h_flags[0]) return fail(ctx, AERL_EINVAL, "x holds a non-finite value");
-  if (h_flags[1]) return fail(ctx, AERL_EINVAL, "y holds a label outside [0, %d)", nc);
-
-  // Class regions, each padded to whole tiles, in class order.
+  const int32_t *head = ctx->upload_head;
+  if (head[nc + 1]) return fail(ctx, AERL_EINVAL, "x holds a non-finite value");
+  if (head[nc]) return fail(ctx, AERL_EINVAL, "y holds a label outside [0, %d)", nc);
   int64_t counts[AERL_MAX_CLASSES] = {};
-  for (int c = 0; c < nc; ++c)
-    for (int64_t b = 0; b < M.n_blocks; ++b) counts[c] += h_counts[b * nc + c];
+  for (int c = 0; c < nc; ++c) counts[c] = head[c];
   set_regions(d, counts);
   if (d.n_pad > M.n_pad_max) return fail(ctx, AERL_EINVAL, "internal: layout overflow");
-  for (int c = 0; c < nc; ++c) {
-    const int64_t tile = d.region_tile0[c];
-    for (int64_t t = 0; t < d.region_tiles[c]; ++t) {
-      const int64_t valid = std::min<int64_t>(AERL_TILE, counts[c] - t * AERL_TILE);
-      h_tiles[tile + t] = c | (int32_t)(valid << 8);
-    }
-    int64_t run = tile * AERL_TILE;
-    for (int64_t b = 0; b < M.n_blocks; ++b) {
-      h_base[b * nc + c] = (int32_t)run;
-      run += h_counts[b * nc + c];
-    }
-  }
-  // The x_fm rows use stride n_pad.
-  if (d.n_tiles) AERL_HIP(ctx, hipMemcpyAsync(d.tile_info, h_tiles, (size_t)d.n_tiles * 4, hipMemcpyHostToDevice, stream));
-  if (nbc) AERL_HIP(ctx, hipMemcpyAsync(base_dev, h_base, nbc * 4, hipMemcpyHostToDevice, stream));
-  AERL_HIP(ctx, launch_fill_i32(reinterpret_cast<int32_t *>(d.x_fm), (int64_t)nf * d.n_pad, 0, stream));
-  AERL_HIP(ctx, launch_fill_i32(d.y_pad, d.n_pad, -1, stream));
-  AERL_HIP(ctx, launch_fill_i32(d.perm, d.n_pad, -1, stream));
-  AERL_HIP(ctx, launch_scatter_transpose(x, y, n, nf, nc, base_dev, d.x_fm, d.y_pad, d.perm, d.n_pad,
-                                         M.n_blocks, stream));
-  AERL_HIP(ctx, launch_tau(d.x_fm, d.tile_info, d.n_pad, nf, n,
-                           reinterpret_cast<double *>(base + M.tpart_off), d.tau, stream));
-  AERL_HIP(ctx, hipStreamSynchronize(stream));
   const int32_t id = ctx->next_id++;
   ctx->datasets[id] = d;
   *dataset_id = id;

@@ -185,6 +185,7 @@ struct aerl_ctx {
   void *hard_part = nullptr;
   size_t hard_part_bytes = 0;
   hipEvent_t hard_part_done = nullptr;
+  int32_t *upload_head = nullptr;  // pinned copy of an upload's counts and flags
   // pinned staging buffers of released populations, reused by later packs
   // (pinning host memory costs far more than packing into it)
   std::vector<std::pair<void *, size_t>> staging_pool;
@@ -240,19 +241,29 @@ inline int64_t hard_block_count(const DatasetRec &ds, int sets_per_chunk, int32_
 hipError_t launch_predict(const PopRec &pop, int32_t set, const float *rows, int64_t n,
                           int32_t *pred, hipStream_t s);
 
-// Upload steps (layout.hip)
-hipError_t launch_validate_count(const float *x, const int32_t *y, int64_t n, int32_t nf,
-                                 int32_t nc, int32_t *block_counts, int32_t *flags,
-                                 int64_t n_blocks, hipStream_t s);
-hipError_t launch_scatter_transpose(const float *x, const int32_t *y, int64_t n, int32_t nf,
-                                    int32_t nc, const int32_t *block_base, float *x_fm,
-                                    int32_t *y_pad, int32_t *perm, int64_t n_pad,
-                                    int64_t n_blocks, hipStream_t s);
-// tau from the resident layout: part holds 2 * nf * kTauParts doubles.
-constexpr int kTauParts = 64;
-hipError_t launch_tau(const float *x_fm, const int32_t *tile_info, int64_t n_pad, int32_t nf,
-                      int64_t n, double *part, float *tau, hipStream_t s);
-constexpr int kUploadBlock = 256;  // samples per block in the upload kernels
+// Upload (layout.hip): rows per group of the grouping pass, groups, and
+// blocks (each writes its partial moments of every column).
+constexpr int32_t kUploadParts = 512;  // two 512-thread blocks per CU
+struct UploadShape {
+  int32_t rows, parts;
+  int64_t n_groups;
+};
+UploadShape upload_shape(int64_t n, int32_t nf);
+struct UploadLaunch {
+  const float *x;
+  const int32_t *y;
+  int64_t n;
+  int32_t nf, nc;
+  int32_t *counts;  // [nc + 1][n_groups] scratch
+  int32_t *head;    // [nc + 2]: class totals, bad labels, whether x has a non-finite value
+  double *part;     // [nf][3][parts] scratch
+  float *x_fm;
+  int32_t *y_pad, *perm, *tile_info;
+  float *tau;       // tau[nf], then 1/tau
+};
+// Writes the whole layout and head; with bad labels or features the layout
+// is incomplete (and in bounds).
+hipError_t launch_upload(const UploadLaunch &u, hipStream_t s);
 
 // LDS of one CU, and the most dynamic LDS a hard-eval block may ask for (the
 // rest is left for the kernels' own __shared__ words).
