@@ -89,14 +89,17 @@ int64_t batch_task_count(const DatasetRec &ds, int32_t n_sets, const BatchSplit 
 // CUs, never more blocks than work items).
 void emit_batch_tables(const BatchTables &t, void *img, char *dev, int n_cu, BatchLaunch *l);
 
-// Prediction work of a batch: one 64-thread block per task of 64*S rows.
+// Prediction work of a batch: a task is S x 64 rows of one request, a block
+// for each 64.
+constexpr int kPredictTaskTiles = 4;
 struct PredictTask {
   const float *rows;  // device [n][nf] row-major
   const int4 *set;    // device set record of the rule set to apply
   const uint4 *conds; // device record stream of its population
   int32_t *out;       // device [n]
   int64_t n, row0;    // rows of the request, first row of this task
-  int32_t nf, S;
+  int32_t heads;      // its head table, in records from conds
+  int16_t nf, S;
 };
 struct PredictLaunch {
   const PredictTask *tasks;
@@ -104,6 +107,6 @@ struct PredictLaunch {
   size_t lds;
 };
 hipError_t launch_predict_batch(const PredictLaunch &p, hipStream_t st);
-int predict_samples_per_lane(int32_t nf);  // 4, or 1 when a 256-row tile does not fit LDS
+int predict_task_tiles(int32_t nf);  // S of a task: 4, or 1 for wide tables
 
 }  // namespace aerl

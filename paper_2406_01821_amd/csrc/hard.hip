@@ -23,6 +23,9 @@ namespace aerl {
 namespace {
 
 constexpr int kHardBlock = 1024;
+constexpr int kPredictBlock = 1024;
+constexpr int64_t kPredictWideRows = 1 << 18;
+constexpr int kPredictWideFeatures = 32;
 
 struct HardArgs {
   const float *x_fm;
@@ -159,14 +162,18 @@ __global__ __launch_bounds__(kReduceBlock) void k_hard_reduce(
   emit();
 }
 
-// Prediction for one rule set over row-major rows: one wave per 64*S rows.
+// Prediction for one rule set over row-major rows, 64 S rows per block.
 template <int S>
-__global__ __launch_bounds__(64) void k_predict(const float *__restrict__ rows, int64_t n,
-                                                int32_t nf, const int4 *__restrict__ sets,
-                                                int32_t set_idx, const uint4 *__restrict__ conds,
-                                                int32_t *__restrict__ out) {
-  extern __shared__ __align__(16) float xs[];  // [nf][64*S]
-  predict_block<S>(rows, n, nf, ldc(sets, set_idx), conds, out, (int64_t)blockIdx.x * 64 * S, xs);
+__global__ __launch_bounds__(kPredictBlock) void k_predict(const float *__restrict__ rows, int64_t n,
+                                                           int32_t nf, const int4 *__restrict__ sets,
+                                                           int32_t set_idx,
+                                                           const uint4 *__restrict__ conds,
+                                                           const uint4 *__restrict__ heads,
+                                                           int32_t *__restrict__ out) {
+  extern __shared__ __align__(16) float xs[];
+  __shared__ int32_t first[kPredictRows * S];
+  predict_block<S>(rows, n, nf, ldc(sets, set_idx), conds, heads, out,
+                   (int64_t)blockIdx.x * kPredictRows * S, xs, first);
 }
 
 template <int S>
@@ -244,17 +251,30 @@ hipError_t launch_hard_reduce(const HardLaunch &h, int n_cu, hipStream_t st) {
 hipError_t launch_predict(const PopRec &pop, int32_t set, const float *rows, int64_t n,
                           int32_t *pred, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  if ((size_t)pop.nf * 256 * 4 <= kDynLdsMax) {
-    const int64_t blocks = (n + 255) / 256;
-    hipLaunchKernelGGL(k_predict<4>, dim3((unsigned)blocks), dim3(64), (size_t)pop.nf * 256 * 4,
-                       st, rows, n, pop.nf, pop.sets, set, pop.hconds, pred);
-  } else if ((size_t)pop.nf * 64 * 4 <= kDynLdsMax) {
-    const int64_t blocks = (n + 63) / 64;
-    hipLaunchKernelGGL(k_predict<1>, dim3((unsigned)blocks), dim3(64), (size_t)pop.nf * 64 * 4,
-                       st, rows, n, pop.nf, pop.sets, set, pop.hconds, pred);
-  } else {
-    return hipErrorInvalidValue;
-  }
+  // Four rows per lane once 64-row blocks would fill the GPU several times
+  // over, on tables narrow enough to keep 16 waves per CU (2^20 rows x 8
+  // features, 32 rules: 42 us with one row per lane, 23 with four; x 32
+  // features 62 us, one wave per 256 rows walking every rule took 202).
+  const int S = n >= kPredictWideRows && pop.nf <= kPredictWideFeatures ? 4 : 1;
+  const size_t lds = predict_lds(pop.nf, S);
+  const int64_t blocks = (n + kPredictRows * S - 1) / (kPredictRows * S);
+  if (lds > kDynLdsMax) return hipErrorInvalidValue;
+  // A wave per rule while all blocks are resident at once (latency: 4096 rows
+  // x 64 features 9.3 us).  Larger requests take fewer waves per block, whose
+  // walks end once every row is decided, but enough for 16 per CU under the
+  // LDS of their rows.
+  constexpr int64_t kResidentWaves = 256 * 32;
+  int waves = 1, least = 1;
+  while (waves < kPredictBlock / 64 && waves < std::max(pop.max_rules, 4)) waves *= 2;
+  while (least < 16 && least * (int)(kLdsPerCu / lds) < 16) least *= 2;
+  while (waves > least && blocks * waves > kResidentWaves) waves /= 2;
+  const dim3 grid((unsigned)blocks), block((unsigned)waves * 64);
+  if (S == 4)
+    hipLaunchKernelGGL(k_predict<4>, grid, block, lds, st, rows, n, pop.nf, pop.sets, set, pop.hconds,
+                       pop.heads, pred);
+  else
+    hipLaunchKernelGGL(k_predict<1>, grid, block, lds, st, rows, n, pop.nf, pop.sets, set, pop.hconds,
+                       pop.heads, pred);
   return hipGetLastError();
 }
 

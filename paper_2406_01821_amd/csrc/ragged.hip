@@ -65,16 +65,17 @@ __global__ __launch_bounds__(kBatchBlock) AERL_HARD_SGPR_CAP void k_hard_batch(
   }
 }
 
-// Batched prediction: block b runs task b (64*S rows of one request).
-__global__ __launch_bounds__(64) void k_predict_batch(const PredictTask *__restrict__ tasks) {
+// Batched prediction: block (b, s) runs rows 64 s .. 64 s + 63 of task b.
+constexpr int kPredictBatchBlock = 512;
+__global__ __launch_bounds__(kPredictBatchBlock) void k_predict_batch(
+    const PredictTask *__restrict__ tasks) {
   extern __shared__ __align__(16) float xs[];
+  __shared__ int32_t first[kPredictRows];
   const PredictTask t = tasks[blockIdx.x];
-  const int4 set = ldc(t.set, 0);
-  if (t.S == 4) {
-    predict_block<4>(t.rows, t.n, t.nf, set, t.conds, t.out, t.row0, xs);
-  } else {
-    predict_block<1>(t.rows, t.n, t.nf, set, t.conds, t.out, t.row0, xs);
-  }
+  const int64_t row0 = t.row0 + (int64_t)blockIdx.y * kPredictRows;
+  if ((int)blockIdx.y >= t.S || row0 >= t.n) return;  // the whole block
+  predict_block<1>(t.rows, t.n, t.nf, ldc(t.set, 0), t.conds, t.conds + t.heads, t.out, row0, xs,
+                   first);
 }
 
 }  // namespace
@@ -82,7 +83,8 @@ __global__ __launch_bounds__(64) void k_predict_batch(const PredictTask *__restr
 hipError_t launch_predict_batch(const PredictLaunch &p, hipStream_t st) {
   if (p.n_tasks <= 0) return hipSuccess;
   if (p.lds > kDynLdsMax) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_predict_batch, dim3((unsigned)p.n_tasks), dim3(64), p.lds, st, p.tasks);
+  hipLaunchKernelGGL(k_predict_batch, dim3((unsigned)p.n_tasks, kPredictTaskTiles),
+                     dim3(kPredictBatchBlock), p.lds, st, p.tasks);
   return hipGetLastError();
 }
 

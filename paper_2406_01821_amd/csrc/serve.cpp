@@ -23,6 +23,7 @@
 #include <thread>
 
 #include "batch.h"
+#include "predict_block.h"
 #include "serve_sched.h"
 
 namespace aerl {
@@ -185,9 +186,9 @@ bool Serve::launch_one(std::unique_lock<std::mutex> &lk, Slot &slot) {
       src.push_back({r->ds, r->rec.n_sets, reinterpret_cast<const int4 *>(r->image.data()), dsets,
                      dconds, dheads, c, cf, r->rec.n_cat > 0});
     } else {
-      const int S = predict_samples_per_lane(r->nf);
-      plds = std::max(plds, (size_t)r->nf * 64 * S * 4);
-      for (int64_t row0 = 0; row0 < r->n_rows; row0 += 64 * S) {
+      const int S = predict_task_tiles(r->nf);
+      plds = std::max(plds, predict_lds(r->nf));
+      for (int64_t row0 = 0; row0 < r->n_rows; row0 += kPredictRows * S) {
         PredictTask t{};
         t.rows = reinterpret_cast<const float *>(dev + r->rows_off);
         t.set = dsets + r->set_index;
@@ -195,8 +196,9 @@ bool Serve::launch_one(std::unique_lock<std::mutex> &lk, Slot &slot) {
         t.out = reinterpret_cast<int32_t *>(dev + r->out_off);
         t.n = r->n_rows;
         t.row0 = row0;
-        t.nf = r->nf;
-        t.S = S;
+        t.heads = (int32_t)(dheads - dconds);
+        t.nf = (int16_t)r->nf;
+        t.S = (int16_t)S;
         ptasks.push_back(t);
       }
     }
@@ -522,8 +524,8 @@ aerl_status aerl_serve_submit(aerl_ctx *ctx, const aerl_request *req, uint64_t *
     if (r->n_rows > 0) r->rows.assign(req->rows, req->rows + (size_t)r->n_rows * r->nf);
     r->in_bytes = al(r->L.total) + al((size_t)r->n_rows * r->nf * 4);
     r->out_bytes = al((size_t)r->n_rows * 4);
-    const int S = predict_samples_per_lane(r->nf);
-    r->table_bytes = (size_t)((r->n_rows + 64 * S - 1) / (64 * S)) * sizeof(PredictTask);
+    const int S = predict_task_tiles(r->nf);
+    r->table_bytes = (size_t)((r->n_rows + kPredictRows * S - 1) / (kPredictRows * S)) * sizeof(PredictTask);
     r->nominal = (double)r->n_rows * (double)hsets[r->set_index].w;
   }
   std::lock_guard<std::recursive_mutex> lk(ctx->mu);
