@@ -797,19 +797,21 @@ __global__ __launch_bounds__(kBwdWaves * 64) void k_soft_bwd(const SoftArgs a) {
   }
 }
 
-// Adjoint for rule sets of at most RMAX rules with S samples per lane: the
-// per-rule state kept between the two sweeps is l_k = a_k + (survival
-// before k) and log2(1 - r_k), two RMAX x S arrays of floats per lane, read
-// and written through a uniform branch chain on k; at the 64-VGPR budget of
-// eight waves per SIMD the compiler keeps them in per-lane private memory
-// (scratch, served by the vector caches) for RMAX = 16 with four samples per
-// lane.  The reverse sweep recomputes every condition once for its
-// sigmoid(-z); only a rule of the label adds its conditions up again, for
-// the a_k of the U recurrence (the other rules' step of it needs
-// log2(1 - r_k) alone).  Per condition the S slots are summed in the lane; two
-// conditions' sums go over the wave in one reduction (wave_totals4), and the
-// lane that ends each adds it to the block's LDS accumulators (one writer per
-// rule set and tile).
+// Adjoint for rule sets of at most kRegRules rules with S samples per lane:
+// the per-rule state kept between the two sweeps is l_k = a_k + (survival
+// before k) and log2(1 - r_k), in per-lane private memory (scratch, served by
+// the vector caches: only the rows of a set's own rules are touched, so the
+// bound costs nothing below it).  The reverse sweep recomputes every
+// condition once for its sigmoid(-z); only a rule of the label adds its
+// conditions up again, for the a_k of the U recurrence (the other rules' step
+// of it needs log2(1 - r_k) alone).  Per condition the S slots are summed in
+// the lane; two conditions' sums go over the wave in one reduction
+// (wave_totals4), and the lane that ends each adds it to the block's LDS
+// accumulators (one writer per rule set and tile).  Eight waves per SIMD (two
+// blocks per CU) at 64 VGPRs and 80 SGPRs: sets of up to 24 rules on 20,011 x
+// 45 take 234 us (520 us with two samples per lane, 124 VGPRs and one block
+// per CU), of 10-16 rules on 60,000 x 90 0.83 ms (1.39 ms likewise).
+constexpr int kRegRules = 64;
 // The reverse sweep over one rule's conditions, two at a time: their four
 // sums over the wave in one reduction (wave_totals4), added (negated when
 // neg) to the rule set's block accumulators accq by the lane that holds each
@@ -866,42 +868,31 @@ __device__ __forceinline__ void bwd_rule_conds(const SoftArgs &a, const float *x
   }
 }
 
-template <int K, int RMAX, int S>
-__device__ __forceinline__ void l_get(const float (&L)[RMAX][S], int k, float (&out)[S]) {
-  if constexpr (K < RMAX) {
-    if (k == K) {
+// Per-rule state of a lane's S samples, indexed by the rule: private memory,
+// the address the same for the whole wave.  Rules run fastest, so that a
+// rule's S values are S single accesses: one of 4 S bytes would need its
+// registers in a row, which the adjoints at 64 VGPRs do not have.
+template <int S>
+struct RuleState {
+  float v[S][kRegRules];
+  __device__ __forceinline__ void get(int k, float (&out)[S]) const {
 #pragma unroll
-      for (int s = 0; s < S; ++s) out[s] = L[K][s];
-    } else {
-      l_get<K + 1, RMAX, S>(L, k, out);
-    }
+    for (int s = 0; s < S; ++s) out[s] = v[s][k];
   }
-}
-template <int K, int RMAX, int S>
-__device__ __forceinline__ void l_set(float (&L)[RMAX][S], int k, const float (&v)[S]) {
-  if constexpr (K < RMAX) {
-    if (k == K) {
+  __device__ __forceinline__ void set(int k, const float (&in)[S]) {
 #pragma unroll
-      for (int s = 0; s < S; ++s) L[K][s] = v[s];
-    } else {
-      l_set<K + 1, RMAX, S>(L, k, v);
-    }
+    for (int s = 0; s < S; ++s) v[s][k] = in[s];
   }
-}
+};
 
 // 16 waves share a block's tile and accumulators in LDS, so the LDS limit
 // still leaves 32 waves per CU.
 constexpr int kBwdRegBlock = 1024;
 
-// Eight waves per SIMD (two blocks per CU) need at most 64 VGPRs and 80
-// SGPRs per wave (the SGPR bound measured on gfx950): k_soft_bwd_reg is held
-// to that; the variants that keep two samples per lane over 16 or 32 rules
-// would spill VGPRs at that size and run as k_soft_bwd_reg_wide, one block
-// per CU.
-
 // TONLY: the population has threshold conditions only (no x[g] rows).
-template <int S, int RMAX, class Acc, bool TONLY>
-__device__ __forceinline__ void soft_bwd_reg(const SoftArgs &a) {
+template <int S, class Acc, bool TONLY>
+__global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_soft_bwd_reg(
+    const SoftArgs a) {
   constexpr int TS = 64 * S, WPT = AERL_TILE / TS;
   extern __shared__ __align__(16) float smem[];
   float *xs = smem;                                             // [nf][TS]
@@ -941,7 +932,7 @@ __device__ __forceinline__ void soft_bwd_reg(const SoftArgs &a) {
       const int dflt = ldc(a.sets, q0 + q).z;
       const int set_end = ss.z + ss.w;
       Window win = first_window(a);
-      float L[RMAX][S], B[RMAX][S];
+      RuleState<S> L, B;
       float logpy[S], surv[S];
 #pragma unroll
       for (int s = 0; s < S; ++s) { logpy[s] = kNegInf; surv[s] = 0.0f; }
@@ -963,8 +954,8 @@ __device__ __forceinline__ void soft_bwd_reg(const SoftArgs &a) {
           if (hit) logpy[s] = lse(logpy[s], lk[s]);
           surv[s] += b2;
         }
-        l_set<0, RMAX, S>(L, k, lk);
-        l_set<0, RMAX, S>(B, k, bk);
+        L.set(k, lk);
+        B.set(k, bk);
       }
       float gate[S], U[S];
 #pragma unroll
@@ -990,8 +981,8 @@ __device__ __forceinline__ void soft_bwd_reg(const SoftArgs &a) {
         // U, the log2 of a probability, can round to just above 0: 1 - 2^U
         // is then taken as 0.
         float lk[S], bk[S], pre[S];
-        l_get<0, RMAX, S>(L, k, lk);
-        l_get<0, RMAX, S>(B, k, bk);
+        L.get(k, lk);
+        B.get(k, bk);
         bool quiet = true;  // every term of the rule is 0 as computed
 #pragma unroll
         for (int s = 0; s < S; ++s) {
@@ -1027,17 +1018,6 @@ __device__ __forceinline__ void soft_bwd_reg(const SoftArgs &a) {
       a.part_grad[((int64_t)blockIdx.y * a.n_conds + ss.z) * 2 + i] =
           acc[(size_t)q * a.max_set_conds * 2 + i];
   }
-}
-
-template <int S, int RMAX, class Acc, bool TONLY>
-__global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_soft_bwd_reg(
-    const SoftArgs a) {
-  soft_bwd_reg<S, RMAX, Acc, TONLY>(a);
-}
-
-template <int S, int RMAX, class Acc, bool TONLY>
-__global__ __launch_bounds__(kBwdRegBlock) void k_soft_bwd_reg_wide(const SoftArgs a) {
-  soft_bwd_reg<S, RMAX, Acc, TONLY>(a);
 }
 
 // One block per rule set: sums the group partials of its conditions in a
@@ -1084,8 +1064,8 @@ __global__ void k_soft_bwd_final(const float *__restrict__ part, int32_t n_group
 
 struct SoftPlan {
   int S, Q, TG, n_groups;
-  int rmax;  // backward: rule bound of the register-resident kernel, 0 = general kernel
-  int waves; // LDS-state kernels: waves per block
+  bool reg;   // backward: per-rule state in private memory, else in LDS
+  int waves;  // LDS-state kernels: waves per block
   size_t lds;
 };
 
@@ -1156,7 +1136,9 @@ int sets_per_block(int n_sets, int64_t groups, int64_t target, int min_q) {
 
 SoftPlan plan_forward(const DatasetRec &ds, const PopRec &pop) {
   SoftPlan p{};
-  p.S = 4;
+  // four samples per lane while three blocks fit a CU (60,000 x 60, where two
+  // would: 611 us, with two samples per lane 560 us), then two while two fit
+  p.S = tile_lds(ds.nf, 4) <= kLdsPerCu / 3 ? 4 : 2;
   while (p.S > 1 && (size_t)ds.nf * 256 * p.S > 64 * 1024) p.S >>= 1;
   p.Q = sets_per_block(pop.n_sets, count_groups(ds, 1), kFwdTargetBlocks, kSoftBlock / 64);
   p.TG = tiles_per_group(ds, (pop.n_sets + p.Q - 1) / p.Q, kFwdTargetBlocks,
@@ -1166,30 +1148,35 @@ SoftPlan plan_forward(const DatasetRec &ds, const PopRec &pop) {
   return p;
 }
 
-// Backward: the register-resident kernel when the longest rule set has at
-// most 32 rules (bound 8 or 16: four samples per lane; 32: two), else the
-// general kernel with per-rule state in LDS (one sample per lane).
-SoftPlan plan_backward(const DatasetRec &ds, const PopRec &pop) {
+// Plan of an LDS-state adjoint kernel (one sample per lane).
+SoftPlan plan_lds_state(const DatasetRec &ds, const PopRec &pop, SoftPlan p, int max_waves) {
+  p.reg = false;
+  p.S = 1;
+  lds_state_plan(p, (size_t)ds.nf * 64 * 4, (size_t)std::max(pop.max_set_conds, 1) * 2 * 4,
+                 (size_t)std::max(pop.max_rules, 1) * 128 * 4, max_waves, 16, pop.n_sets);
+  return p;
+}
+
+// Backward: per-rule state in private memory up to kRegRules rules (max_s or
+// fewer samples per lane, so that a tile takes at most 64 KiB), else in LDS.
+SoftPlan plan_adjoint(const DatasetRec &ds, const PopRec &pop, int max_s, int lds_waves) {
   SoftPlan p{};
-  const int R = std::max(pop.max_rules, 1);
   const size_t per_set = (size_t)std::max(pop.max_set_conds, 1) * 2 * 4;
   p.TG = tiles_per_group(ds, (pop.n_sets + 63) / 64, kBwdTargetBlocks,
                          (size_t)std::max(pop.n_conds, 1) * 2 * sizeof(float), kBwdPartMax);
   p.n_groups = (int)count_groups(ds, p.TG);
-  p.rmax = R <= 8 ? 8 : R <= 16 ? 16 : R <= 32 ? 32 : 0;
-  if (p.rmax > 0) {
-    p.S = p.rmax <= 16 ? 4 : 2;
-    while (p.S > 1 && (size_t)ds.nf * 256 * p.S > 64 * 1024) p.S >>= 1;
-    const size_t xs = tile_lds(ds.nf, p.S);
-    p.Q = sets_per_block(pop.n_sets, p.n_groups, kBwdTargetBlocks, kBwdRegBlock / 64);
-    while (p.Q > 1 && xs + p.Q * per_set > kLdsPerCu / 2 - kStaticLds) p.Q >>= 1;  // two blocks per CU
-    p.lds = xs + (size_t)p.Q * per_set;
-    if (p.lds <= kDynLdsMax) return p;
-  }
-  p.rmax = 0;
-  p.S = 1;
-  lds_state_plan(p, (size_t)ds.nf * 64 * 4, per_set, (size_t)R * 128 * 4, kBwdWaves, 16, pop.n_sets);
+  if (pop.max_rules > kRegRules) return plan_lds_state(ds, pop, p, lds_waves);
+  p.reg = true;
+  p.S = max_s;
+  while (p.S > 1 && (size_t)ds.nf * 256 * p.S > 64 * 1024) p.S >>= 1;
+  const size_t xs = tile_lds(ds.nf, p.S);
+  p.Q = sets_per_block(pop.n_sets, p.n_groups, kBwdTargetBlocks, kBwdRegBlock / 64);
+  while (p.Q > 1 && xs + p.Q * per_set > kLdsPerCu / 2 - kStaticLds) p.Q >>= 1;  // two blocks per CU
+  p.lds = xs + (size_t)p.Q * per_set;
   return p;
+}
+SoftPlan plan_backward(const DatasetRec &ds, const PopRec &pop) {
+  return plan_adjoint(ds, pop, 4, kBwdWaves);
 }
 
 void fill_args(SoftArgs &a, const SoftLaunch &l, const SoftPlan &p) {
@@ -1235,29 +1222,20 @@ void launch_fwd(const SoftPlan &p, dim3 grid, hipStream_t st, const SoftArgs &a)
 template <class Acc, bool TONLY>
 void launch_bwd_reg(const SoftPlan &p, dim3 grid, hipStream_t st, const SoftArgs &a) {
   const dim3 rb(kBwdRegBlock);
-  if (p.rmax == 8 && p.S == 4) {
-    hipLaunchKernelGGL((k_soft_bwd_reg<4, 8, Acc, TONLY>), grid, rb, p.lds, st, a);
-  } else if (p.rmax == 8 && p.S == 2) {
-    hipLaunchKernelGGL((k_soft_bwd_reg<2, 8, Acc, TONLY>), grid, rb, p.lds, st, a);
-  } else if (p.rmax == 16 && p.S == 4) {
-    hipLaunchKernelGGL((k_soft_bwd_reg<4, 16, Acc, TONLY>), grid, rb, p.lds, st, a);
-  } else if (p.rmax == 16 && p.S == 2) {
-    hipLaunchKernelGGL((k_soft_bwd_reg_wide<2, 16, Acc, TONLY>), grid, rb, p.lds, st, a);
-  } else if (p.rmax == 32 && p.S == 2) {
-    hipLaunchKernelGGL((k_soft_bwd_reg_wide<2, 32, Acc, TONLY>), grid, rb, p.lds, st, a);
-  } else if (p.rmax == 8) {  // one sample per lane (wide datasets)
-    hipLaunchKernelGGL((k_soft_bwd_reg<1, 8, Acc, TONLY>), grid, rb, p.lds, st, a);
-  } else if (p.rmax == 16) {
-    hipLaunchKernelGGL((k_soft_bwd_reg<1, 16, Acc, TONLY>), grid, rb, p.lds, st, a);
-  } else {
-    hipLaunchKernelGGL((k_soft_bwd_reg<1, 32, Acc, TONLY>), grid, rb, p.lds, st, a);
+  switch (p.S) {
+    case 4: hipLaunchKernelGGL((k_soft_bwd_reg<4, Acc, TONLY>), grid, rb, p.lds, st, a); break;
+    case 2: hipLaunchKernelGGL((k_soft_bwd_reg<2, Acc, TONLY>), grid, rb, p.lds, st, a); break;
+    default: hipLaunchKernelGGL((k_soft_bwd_reg<1, Acc, TONLY>), grid, rb, p.lds, st, a); break;
   }
 }
 
 }  // namespace
 
+// Sets past 32 rules are bounded by the LDS-state kernel's one-wave form,
+// whichever kernel runs them.
 bool soft_backward_supported(const DatasetRec &ds, const PopRec &pop) {
-  return plan_backward(ds, pop).lds <= kDynLdsMax;
+  return (pop.max_rules <= 32 || plan_lds_state(ds, pop, SoftPlan{}, 1).lds <= kDynLdsMax) &&
+         plan_backward(ds, pop).lds <= kDynLdsMax;
 }
 
 namespace {
@@ -1372,12 +1350,11 @@ __device__ __forceinline__ float smax_log2py(const float (&v)[NC], int nc, float
   return ty - m - flog2(sum);
 }
 
-constexpr int kSmaxFwdS = 2;
 constexpr int kSmaxBwdWaves = 4;
 
-template <int NC, class Acc, bool TONLY>
+template <int S, int NC, class Acc, bool TONLY>
 __global__ __launch_bounds__(kSoftBlock) AERL_SOFT_SGPR_CAP void k_smax_fwd(const SoftArgs a, float beta2) {
-  constexpr int S = kSmaxFwdS, TS = 64 * S, WPT = AERL_TILE / TS;
+  constexpr int TS = 64 * S, WPT = AERL_TILE / TS;
   extern __shared__ __align__(16) float smem[];
   float *xs = smem;
   float2 *ext = reinterpret_cast<float2 *>(smem + (size_t)a.nf * TS);  // [nf]
@@ -1451,7 +1428,7 @@ __global__ __launch_bounds__(kSoftBlock) AERL_SOFT_SGPR_CAP void k_smax_fwd(cons
     a.part_loss[(int64_t)blockIdx.y * a.n_sets + q0 + i] = acc[i];
 }
 
-template <int NC, class Acc, bool TONLY>
+template <int NC, class Acc>
 __global__ __launch_bounds__(kSmaxBwdWaves * 64) void k_smax_bwd(const SoftArgs a, float beta,
                                                                  float beta2) {
   constexpr int TS = 64, WPT = AERL_TILE / TS;
@@ -1537,12 +1514,8 @@ __global__ __launch_bounds__(kSmaxBwdWaves * 64) void k_smax_bwd(const SoftArgs 
         Acc ra;
         for (int j = r.x; j < r.x + r.y; ++j) {
           float z[1], xf[1], xg[1];
-          if constexpr (TONLY) {
-            cond_z_t<1>(a, xs, lane, j, z, xf, xg);
-          } else {
-            bool ff;
-            cond_z<1>(a, xs, lane, j, z, xf, xg, ff);
-          }
+          bool ff;
+          cond_z<1>(a, xs, lane, j, z, xf, xg, ff);
           const float t = ra.add(z[0]);
           // dL/dz = dL/dr_k * r_k * sigmoid(-z)
           const float dz = drk * acc_sig_neg(ra, a2k, z[0], t);
@@ -1582,22 +1555,20 @@ __global__ __launch_bounds__(kSmaxBwdWaves * 64) void k_smax_bwd(const SoftArgs 
   }
 }
 
-// Adjoint of the softmax head for rule sets of at most 16 rules and at most
-// four classes, four samples per lane, 16 waves per block: the per-rule
-// state between the two sweeps (log2 r_k, the prefix sum of log2(1 - r_i)
-// before k and log2(1 - r_k), for each of the lane's samples) is a
-// 16 x 4 x 3 array per lane, read and written through a uniform branch chain
-// on k (the compiler keeps it in per-lane private memory at the 64-VGPR
-// budget of two blocks per CU).  The reverse sweep needs each condition's
-// sigmoid(-z) alone, so it adds no condition up again; the conditions' sums
-// go over the wave and to LDS as in the first-firing adjoint.  Same
-// formulas as k_smax_bwd.
-constexpr int kSmaxRegRules = 16;
-
-template <int NC, class Acc, bool TONLY>
+// Adjoint of the softmax head for rule sets of at most kRegRules rules, 16
+// waves per block: the per-rule state between the two sweeps (log2 r_k, the
+// prefix sum of log2(1 - r_i) before k and log2(1 - r_k), for each of the
+// lane's samples) is in private memory as in the first-firing adjoint; the
+// votes and their gradients take S x NC registers each, at most 16.  The
+// reverse sweep needs each condition's sigmoid(-z) alone, so it adds no
+// condition up again; the conditions' sums go over the wave and to LDS as in
+// the first-firing adjoint.  Same formulas as k_smax_bwd, which takes 4-15
+// times as long (sets of up to 24 rules on 20,011 x 45: 0.97 ms against
+// 0.25).
+template <int S, int NC, class Acc, bool TONLY>
 __global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_smax_bwd_reg(
     const SoftArgs a, float beta, float beta2) {
-  constexpr int S = 4, RMAX = kSmaxRegRules, TS = 64 * S, WPT = AERL_TILE / TS;
+  constexpr int TS = 64 * S, WPT = AERL_TILE / TS;
   extern __shared__ __align__(16) float smem[];
   float *xs = smem;                                             // [nf][TS]
   float2 *ext = reinterpret_cast<float2 *>(xs + (size_t)a.nf * TS);  // [nf]
@@ -1633,7 +1604,7 @@ __global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_smax_bwd
       const int dflt = ldc(a.sets, q0 + q).z;
       const int set_end = ss.z + ss.w;
       Window win = first_window(a);
-      float LA[RMAX][S], LP[RMAX][S], LB[RMAX][S];
+      RuleState<S> LA, LP, LB;
       float v[S][NC], surv[S];
 #pragma unroll
       for (int s = 0; s < S; ++s) {
@@ -1659,9 +1630,9 @@ __global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_smax_bwd
           add_vote(v[s], r.z, fexp2(a2));
           surv[s] += b2;
         }
-        l_set<0, RMAX, S>(LA, k, a2s);
-        l_set<0, RMAX, S>(LP, k, pre);
-        l_set<0, RMAX, S>(LB, k, b2s);
+        LA.set(k, a2s);
+        LP.set(k, pre);
+        LB.set(k, b2s);
       }
       // dL/dv per slot (clamped samples and padding get none); for the
       // label, -beta times the other classes' probabilities
@@ -1688,8 +1659,8 @@ __global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_smax_bwd
         if (!rule_live_back<TONLY>(a, ext, lane, r, ss.z, set_end, kDeadProb, kSatProb, win, act))
           continue;
         float la[S], lp[S], drk[S];
-        l_get<0, RMAX, S>(LA, k, la);
-        l_get<0, RMAX, S>(LP, k, lp);
+        LA.get(k, la);
+        LP.get(k, lp);
         bool quiet = true;  // every term of the rule is 0 as computed
 #pragma unroll
         for (int s = 0; s < S; ++s) {
@@ -1707,7 +1678,7 @@ __global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_smax_bwd
                                                      false, ra);
         }
         float lb[S];
-        l_get<0, RMAX, S>(LB, k, lb);
+        LB.get(k, lb);
 #pragma unroll
         for (int s = 0; s < S; ++s) tail[s] += lb[s];
       }
@@ -1770,83 +1741,90 @@ __global__ __launch_bounds__(256) void k_smax_proba(const float *__restrict__ ro
 int smax_nc(int nc) { return nc <= 2 ? 2 : nc <= 4 ? 4 : nc <= 8 ? 8 : 16; }
 
 SoftPlan plan_smax_backward(const DatasetRec &ds, const PopRec &pop) {
-  SoftPlan p{};
-  const int R = std::max(pop.max_rules, 1);
-  const size_t per_set = (size_t)std::max(pop.max_set_conds, 1) * 2 * 4;
-  p.TG = tiles_per_group(ds, (pop.n_sets + 63) / 64, kBwdTargetBlocks,
-                         (size_t)std::max(pop.n_conds, 1) * 2 * sizeof(float), kBwdPartMax);
-  p.n_groups = (int)count_groups(ds, p.TG);
-  // up to 16 rules and four classes on at most 64 features: four samples per
-  // lane with the per-rule state in per-lane memory, two blocks per CU
-  if (R <= kSmaxRegRules && smax_nc(ds.nc) <= 4 && (size_t)ds.nf * 256 * 4 <= 64 * 1024) {
-    p.rmax = kSmaxRegRules;
-    p.S = 4;
-    const size_t xs = tile_lds(ds.nf, p.S);
-    p.Q = sets_per_block(pop.n_sets, p.n_groups, kBwdTargetBlocks, kBwdRegBlock / 64);
-    while (p.Q > 1 && xs + p.Q * per_set > kLdsPerCu / 2 - kStaticLds) p.Q >>= 1;
-    p.lds = xs + (size_t)p.Q * per_set;
-    if (p.lds <= kDynLdsMax) return p;
-  }
-  p.rmax = 0;
-  p.S = 1;
-  lds_state_plan(p, (size_t)ds.nf * 64 * 4, per_set, (size_t)R * 128 * 4, kSmaxBwdWaves, 16,
-                 pop.n_sets);
+  return plan_adjoint(ds, pop, std::min(4, 16 / smax_nc(ds.nc)), kSmaxBwdWaves);
+}
+
+// Same groups (and so the same workspace) as the first-firing forward.  Four
+// samples per lane up to four classes and while three blocks fit a CU
+// (20,011 x 45, 150 mixed rule sets: 94 us, with two samples 111 us; 60,000 x
+// 60, where two would fit: 576 and 517 us), else two, one where two and the
+// extremes do not fit.
+SoftPlan plan_smax_forward(const DatasetRec &ds, const PopRec &pop) {
+  SoftPlan p = plan_forward(ds, pop);
+  p.S = smax_nc(ds.nc) <= 4 && tile_lds(ds.nf, 4) <= kLdsPerCu / 3 ? 4 : 2;
+  if (tile_lds(ds.nf, p.S) + (size_t)p.Q * 8 > kDynLdsMax) p.S = 1;
+  p.lds = tile_lds(ds.nf, p.S) + (size_t)p.Q * 8;
   return p;
 }
 
-SoftPlan plan_smax_forward(const DatasetRec &ds, const PopRec &pop) {
-  SoftPlan p = plan_forward(ds, pop);  // same groups (and so the same workspace)
-  p.S = kSmaxFwdS;
-  p.lds = tile_lds(ds.nf, p.S) + (size_t)p.Q * 8;
-  return p;
+template <int S, int NC>
+void launch_smax_fwd_s(const SoftPlan &p, dim3 grid, hipStream_t st, const SoftArgs &a, bool prod,
+                       bool tonly, float beta2) {
+  const dim3 b(kSoftBlock);
+  if (prod && tonly)
+    hipLaunchKernelGGL((k_smax_fwd<S, NC, RuleProd, true>), grid, b, p.lds, st, a, beta2);
+  else if (prod)
+    hipLaunchKernelGGL((k_smax_fwd<S, NC, RuleProd, false>), grid, b, p.lds, st, a, beta2);
+  else if (tonly)
+    hipLaunchKernelGGL((k_smax_fwd<S, NC, RuleAcc, true>), grid, b, p.lds, st, a, beta2);
+  else
+    hipLaunchKernelGGL((k_smax_fwd<S, NC, RuleAcc, false>), grid, b, p.lds, st, a, beta2);
 }
 
 template <int NC>
 void launch_smax_fwd_nc(const SoftPlan &p, dim3 grid, hipStream_t st, const SoftArgs &a, bool prod,
                         bool tonly, float beta2) {
+  if constexpr (NC <= 4) {
+    if (p.S == 4) return launch_smax_fwd_s<4, NC>(p, grid, st, a, prod, tonly, beta2);
+  }
+  if (p.S == 2) return launch_smax_fwd_s<2, NC>(p, grid, st, a, prod, tonly, beta2);
+  launch_smax_fwd_s<1, NC>(p, grid, st, a, prod, tonly, beta2);
+}
+
+template <int S, int NC>
+void launch_smax_bwd_s(const SoftPlan &p, dim3 grid, hipStream_t st, const SoftArgs &a, bool prod,
+                       bool tonly, float beta, float beta2) {
+  const dim3 b(kBwdRegBlock);
   if (prod && tonly)
-    hipLaunchKernelGGL((k_smax_fwd<NC, RuleProd, true>), grid, dim3(kSoftBlock), p.lds, st, a, beta2);
+    hipLaunchKernelGGL((k_smax_bwd_reg<S, NC, RuleProd, true>), grid, b, p.lds, st, a, beta, beta2);
   else if (prod)
-    hipLaunchKernelGGL((k_smax_fwd<NC, RuleProd, false>), grid, dim3(kSoftBlock), p.lds, st, a, beta2);
+    hipLaunchKernelGGL((k_smax_bwd_reg<S, NC, RuleProd, false>), grid, b, p.lds, st, a, beta, beta2);
   else if (tonly)
-    hipLaunchKernelGGL((k_smax_fwd<NC, RuleAcc, true>), grid, dim3(kSoftBlock), p.lds, st, a, beta2);
+    hipLaunchKernelGGL((k_smax_bwd_reg<S, NC, RuleAcc, true>), grid, b, p.lds, st, a, beta, beta2);
   else
-    hipLaunchKernelGGL((k_smax_fwd<NC, RuleAcc, false>), grid, dim3(kSoftBlock), p.lds, st, a, beta2);
+    hipLaunchKernelGGL((k_smax_bwd_reg<S, NC, RuleAcc, false>), grid, b, p.lds, st, a, beta, beta2);
 }
 
 template <int NC>
 void launch_smax_bwd_nc(const SoftPlan &p, dim3 grid, hipStream_t st, const SoftArgs &a, bool prod,
                         bool tonly, float beta, float beta2) {
-  if constexpr (NC <= 4) {
-    if (p.rmax == kSmaxRegRules) {
-      const dim3 rb(kBwdRegBlock);
-      if (prod && tonly)
-        hipLaunchKernelGGL((k_smax_bwd_reg<NC, RuleProd, true>), grid, rb, p.lds, st, a, beta, beta2);
-      else if (prod)
-        hipLaunchKernelGGL((k_smax_bwd_reg<NC, RuleProd, false>), grid, rb, p.lds, st, a, beta, beta2);
-      else if (tonly)
-        hipLaunchKernelGGL((k_smax_bwd_reg<NC, RuleAcc, true>), grid, rb, p.lds, st, a, beta, beta2);
-      else
-        hipLaunchKernelGGL((k_smax_bwd_reg<NC, RuleAcc, false>), grid, rb, p.lds, st, a, beta, beta2);
-      return;
-    }
+  if (!p.reg) {
+    const dim3 b(p.waves * 64);
+    if (prod)
+      hipLaunchKernelGGL((k_smax_bwd<NC, RuleProd>), grid, b, p.lds, st, a, beta, beta2);
+    else
+      hipLaunchKernelGGL((k_smax_bwd<NC, RuleAcc>), grid, b, p.lds, st, a, beta, beta2);
+    return;
   }
-  const dim3 b(p.waves * 64);
-  if (prod && tonly)
-    hipLaunchKernelGGL((k_smax_bwd<NC, RuleProd, true>), grid, b, p.lds, st, a, beta, beta2);
-  else if (prod)
-    hipLaunchKernelGGL((k_smax_bwd<NC, RuleProd, false>), grid, b, p.lds, st, a, beta, beta2);
-  else if (tonly)
-    hipLaunchKernelGGL((k_smax_bwd<NC, RuleAcc, true>), grid, b, p.lds, st, a, beta, beta2);
-  else
-    hipLaunchKernelGGL((k_smax_bwd<NC, RuleAcc, false>), grid, b, p.lds, st, a, beta, beta2);
+  if constexpr (NC <= 4) {
+    if (p.S == 4) return launch_smax_bwd_s<4, NC>(p, grid, st, a, prod, tonly, beta, beta2);
+  }
+  if constexpr (NC <= 8) {
+    if (p.S == 2) return launch_smax_bwd_s<2, NC>(p, grid, st, a, prod, tonly, beta, beta2);
+  }
+  launch_smax_bwd_s<1, NC>(p, grid, st, a, prod, tonly, beta, beta2);
 }
 
 }  // namespace
 
+// Tables wide enough that a forward tile of two samples per lane does not
+// fit are refused, and sets past 16 rules (four classes, 64 features) are
+// bounded by the LDS-state adjoint's one-wave form, whichever kernels run.
 bool smax_supported(const DatasetRec &ds, const PopRec &pop) {
-  return ds.nc <= kSmaxMaxClasses && plan_smax_backward(ds, pop).lds <= kDynLdsMax &&
-         plan_smax_forward(ds, pop).lds <= kDynLdsMax;
+  const bool few = pop.max_rules <= 16 && smax_nc(ds.nc) <= 4 && ds.nf <= 64;
+  return ds.nc <= kSmaxMaxClasses &&
+         (few || plan_lds_state(ds, pop, SoftPlan{}, 1).lds <= kDynLdsMax) &&
+         (size_t)ds.nf * 64 * 2 * 4 + (size_t)plan_forward(ds, pop).Q * 8 <= kDynLdsMax;
 }
 
 hipError_t launch_smax_forward(const SoftLaunch &l, float beta, hipStream_t st) {
@@ -1983,13 +1961,13 @@ hipError_t launch_soft_backward(const SoftLaunch &l, hipStream_t st) {
   if (p.n_groups > 0) {
     const dim3 grid((unsigned)((pop.n_sets + p.Q - 1) / p.Q), (unsigned)p.n_groups);
     const bool prod = pop.max_rule_conds <= kProdMaxConds, tonly = pop.n_ff == 0 && pop.n_cat == 0;
-    if (p.rmax > 0 && prod && tonly) {
+    if (p.reg && prod && tonly) {
       launch_bwd_reg<RuleProd, true>(p, grid, st, a);
-    } else if (p.rmax > 0 && prod) {
+    } else if (p.reg && prod) {
       launch_bwd_reg<RuleProd, false>(p, grid, st, a);
-    } else if (p.rmax > 0 && tonly) {
+    } else if (p.reg && tonly) {
       launch_bwd_reg<RuleAcc, true>(p, grid, st, a);
-    } else if (p.rmax > 0) {
+    } else if (p.reg) {
       launch_bwd_reg<RuleAcc, false>(p, grid, st, a);
     } else {
       hipLaunchKernelGGL(k_soft_bwd, grid, dim3(p.waves * 64), p.lds, st, a);

@@ -81,3 +81,40 @@ def test_far_conditions_change_nothing(ctx, rules, conds):
         got.append([t.cpu().numpy() for t in r] + [t.cpu().numpy()[kept] for t in g])
         assert all(not t.cpu().numpy()[~kept].any() for t in g)
     assert all(np.array_equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("n_rules,nc,nf", [(64, 3, 20), (65, 3, 20), (64, 16, 20), (33, 5, 70),
+                                           (64, 4, 130)])
+def test_rule_bound_of_the_private_state(ctx, n_rules, nc, nf):
+    """Adjoints with 64 rules (state in private memory) and one more (state in
+    LDS), at every sample count per lane."""
+    w = synth.tiny(n_rules + nc + nf, n=700, nf=nf, n_classes=nc, n_sets=6,
+                   rules=(n_rules, n_rules), conds=(1, 3), ff_frac=0.3)
+    run_case(ctx, w.data, w.pop)
+    run_softmax(ctx, w.data, w.pop, 2.0)
+
+
+def test_refused_shapes_stay_refused(ctx):
+    """512 features with 64 rules exceed the LDS-state adjoint, 320 features
+    the softmax head's forward tile; 319 features pass it."""
+    import torch
+    from paper_2406_01821_amd.aerl import AerlError
+    for nf, n_rules, soft, smax in ((512, 64, False, False), (320, 2, True, False),
+                                    (319, 2, True, True)):
+        w = synth.tiny(nf, n=300, nf=nf, n_classes=2, n_sets=2, rules=(n_rules, n_rules),
+                       conds=(1, 2))
+        ds = ctx.upload_dataset(w.data)
+        p = ctx.pack_population(w.pop, nf, 2)
+        v = [torch.tensor(a, device=ctx.device) for a in (w.pop.coef, w.pop.coef2, w.pop.theta)]
+        one = torch.ones(2, device=ctx.device)
+        for ok, call in ((soft, lambda: ctx.soft_backward(ds, p, *v, one)),
+                         (smax, lambda: ctx.softmax_forward(ds, p, *v, 2.0)),
+                         (smax, lambda: ctx.softmax_backward(ds, p, *v, 2.0, one))):
+            if ok:
+                call()
+            else:
+                with pytest.raises(AerlError):
+                    call()
+        if smax:
+            run_softmax(ctx, w.data, w.pop, 2.0)
+        torch.cuda.synchronize()
