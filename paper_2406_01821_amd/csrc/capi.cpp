@@ -743,6 +743,7 @@ aerl_status aerl_finetune(aerl_ctx *ctx, int32_t dataset_id, int32_t pop_id,
   t.epochs = cfg->epochs;
   t.optimizer = cfg->optimizer;
   t.lr = cfg->lr; t.beta1 = cfg->beta1; t.beta2 = cfg->beta2; t.eps = cfg->eps;
+  t.n_cu = ctx->n_cu;
   t.ws = ws;
   AERL_HIP(ctx, hipSetDevice(ctx->device));
   AERL_HIP(ctx, run_finetune(t, stream));

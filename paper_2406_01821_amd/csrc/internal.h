@@ -318,6 +318,15 @@ size_t soft_ws_bytes(const DatasetRec &ds, const PopRec &pop, bool backward);
 bool soft_backward_supported(const DatasetRec &ds, const PopRec &pop);
 hipError_t launch_soft_forward(const SoftLaunch &l, hipStream_t s);
 hipError_t launch_soft_backward(const SoftLaunch &l, hipStream_t s);
+// The adjoint kernel alone: partial gradients [n_groups][n_conds][2] and the
+// condition records it reads, both in l.ws; gathers the records first when
+// asked, else they are there from the last call or written by the caller.
+struct SoftParts {
+  const float *grad;
+  uint4 *crec;
+  int32_t n_groups;
+};
+hipError_t launch_soft_adjoint(const SoftLaunch &l, bool gather, SoftParts *out, hipStream_t s);
 // Softmax head (soft.hip): up to kSmaxMaxClasses classes; same workspace as
 // the first-firing soft path (soft_ws_bytes).
 constexpr int kSmaxMaxClasses = 16;
@@ -329,7 +338,7 @@ hipError_t launch_smax_proba(const SoftLaunch &l, int32_t set, float beta, const
 
 // Fine-tuning (tune.hip): workspace layout and the epoch loop.
 struct TuneLayout {
-  size_t soft_off, grad_off, mom_off, dloss_off, total;
+  size_t soft_off, mom_off, total;
 };
 TuneLayout tune_layout(const DatasetRec &ds, const PopRec &pop);
 struct TuneLaunch {
@@ -339,6 +348,7 @@ struct TuneLaunch {
   float *loss_hist;             // [epochs + 1][n_sets] or null
   int32_t epochs, optimizer;
   float lr, beta1, beta2, eps;
+  int n_cu;
   void *ws;
 };
 hipError_t run_finetune(const TuneLaunch &t, hipStream_t s);
