@@ -75,56 +75,84 @@ void set_regions(DatasetRec &d, const int64_t *counts) {
   d.n_pad = tile * AERL_TILE;
 }
 
-// Launch configuration of the plain hard-eval path.  Large set chunks (up to
-// 2048 rule sets per block) over single tiles: every staged tile serves many
-// rule sets, so the per-tile barrier and the restaging of the dataset per
-// chunk are amortized; chunks shrink only when the grid would be too small
-// to fill the GPU (down to about 64 sets, or 32, two per wave of a block,
-// on tables of at most four tiles, whose restaging costs next to nothing:
-// on the 569 x 30 table with 100 sets 11.6 us per call against 13.3 us with
-// 64-set chunks, while the 64-run ragged mix launched run by run slows by
-// 5% with 32-set chunks) or their counters do not fit in LDS.
+// Time of a plain hard-eval launch of single-tile groups with S samples per
+// lane and set chunks of Q, in CU microseconds of an average population.  A
+// block stages its tile (nf * 64 * S floats, 4 / S times), then its 16 waves
+// share the chunk's rule sets; two blocks share a CU where their LDS fits
+// twice.  The second one hides the latency of the record loads and LDS
+// reads at the price of 1.48 times longer visits, and fewer samples per lane
+// make a visit 0.66 (two) or 0.61 (one) of its length for a half or a quarter
+// of the samples.  What a grid costs beyond its work is its last round of
+// blocks: up to one round a launch lasts one block, just above one it lasts
+// two, and each further round adds one (0.6: the mean of a round's start and
+// end, where blocks do not run in step).
+double hard_cost(const DatasetRec &ds, int64_t n_sets, int n_cu, int S, int64_t Q, int per_cu) {
+  const double blocks = (double)std::max<int64_t>(ds.n_tiles, 1) * (double)((n_sets + Q - 1) / Q);
+  const double rounds = blocks / ((double)n_cu * per_cu);
+  const double on_cu = blocks > n_cu ? per_cu : 1;  // of the CU that is done last
+  const double stage = 3.6 + 0.058 * (ds.nf * 0.25 * S);  // latency, then KiB at 18 GB/s
+  const double visit = 1.39 * (on_cu > 1 ? 1.475 : 1.0) * (S == 4 ? 1.0 : S == 2 ? 0.66 : 0.61);
+  const double block = (4 / S) * (stage + std::max(1.0, (double)Q / 16 + 0.5) * visit);
+  return block * (rounds <= 1 ? 1.0 : rounds < 1.4 ? 2.0 : rounds + 0.6);
+}
+
+// Launch configuration of the plain hard-eval path: over single-tile groups,
+// the samples per lane and the chunk of rule sets that hard_cost finds
+// cheapest, among the fewest chunks that the LDS allows (at one or two blocks
+// per CU), up to three more, and those that fill the GPU's workgroup slots
+// once to four times.  The
+// constants of hard_cost were fitted to 39 tables of 3 to 3908 tiles with 20
+// to 300 features and 30 to 4096 rule sets, each timed over its S and Q: its
+// choice is on average 2% (at most 18%) slower than the best of them, where
+// the previous rule (two blocks per CU whenever any S allows it, 4 * n_cu
+// blocks) was 16% slower on average: 50 021 x 97 features x 377 sets 71 us
+// against 129 us, 20 000 x 110 x 3000 118 against 171 us.  Chunks hold at
+// least 32 rule sets, two per wave of a block, on tables of at most four
+// tiles, and 16 on larger ones.
 void hard_config(const DatasetRec &ds, int32_t n_sets, int n_cu, int *S, int *Q, int *TG) {
   const int64_t tiles = std::max<int64_t>(ds.n_tiles, 1);
-  const int64_t target = 4LL * n_cu;
-  const int q_floor = tiles <= 4 ? 32 : 64;
-  int q = (int)std::min<int64_t>(std::max<int32_t>(n_sets, 1), kHardChunkMax);
-  // Two blocks per CU (eight waves per SIMD) hide the latency of the scalar
-  // record loads and LDS reads far better than one: take the most samples per
-  // lane whose tile leaves room for two blocks with a chunk of at least 64
-  // sets (measured: two samples per lane at two blocks beat four at one),
-  // and then the largest chunk that keeps two blocks; with no such S, the
-  // most samples per lane that fit one block.
-  const size_t half = kLdsPerCu / 2 - kStaticLds;
-  const int q_min2 = std::min(q, 64);
+  const int64_t sets = std::max<int32_t>(n_sets, 1);
+  const int64_t q_floor = std::min<int64_t>(sets, tiles <= 4 ? 32 : 16);
+  double best = 0;
+  *S = 0;
+  for (int s = 4; s >= 1; s >>= 1) {
+    for (int per_cu = 2; per_cu >= 1; --per_cu) {
+      const size_t budget = per_cu == 2 ? kLdsPerCu / 2 - kStaticLds : kDynLdsMax;
+      const size_t fixed = hard_block_lds(ds.nf, s, 0, ds.nc, true);
+      const size_t per_set = hard_counter_bytes(1, ds.nc, true);
+      if (fixed + per_set > budget) continue;
+      int64_t q_max = std::min<int64_t>(sets, kHardChunkMax);
+      if (per_set) q_max = std::min<int64_t>(q_max, (int64_t)((budget - fixed) / per_set));
+      const int64_t fewest = (sets + q_max - 1) / q_max;
+      for (int k = 0; k < 8; ++k) {
+        // equal chunks (a short last chunk leaves its blocks underused)
+        const int64_t chunks =
+            k < 4 ? fewest + k : std::max(fewest, (int64_t)(k - 3) * n_cu * per_cu / tiles);
+        const int64_t q = std::min(q_max, std::max(q_floor, (sets + chunks - 1) / chunks));
+        const double cost = hard_cost(ds, sets, n_cu, s, q, per_cu);
+        if (*S == 0 || cost < best) {
+          best = cost;
+          *S = s;
+          *Q = (int)q;
+        }
+      }
+    }
+  }
+  // Single-tile groups (measured fastest: larger groups leave a partly
+  // filled last round of blocks), unless the grid would exceed the launch
+  // limit; then the largest chunk whose 16-bit counters fit and the fewest
+  // tiles per group that fit it.
+  *TG = 1;
+  if (*S && hard_block_count(ds, *Q, n_sets, 1) <= kMaxHardBlocks) return;
   int s = 4;
-  while (s > 1 && hard_block_lds(ds.nf, s, q_min2, ds.nc) > half) s >>= 1;
-  size_t budget = half;
-  if (hard_block_lds(ds.nf, s, q_min2, ds.nc) > half) {
-    s = 4;
-    while (s > 1 && (size_t)ds.nf * 256 * s > 150 * 1024) s >>= 1;
-    budget = kDynLdsMax;
-  }
+  while (s > 1 && (size_t)ds.nf * 256 * s > 150 * 1024) s >>= 1;
+  int q = (int)std::min<int64_t>(sets, kHardChunkMax);
+  while (q > 1 && std::max(hard_block_lds(ds.nf, s, q, ds.nc, false),
+                           hard_block_lds(ds.nf, s, q, ds.nc, true)) > kDynLdsMax)
+    q = (q + 1) / 2;
   *S = s;
-  // Chunk size and tiles per group, planned first for single-tile groups
-  // (10-bit counters) and again with 16-bit counters when the launch limit
-  // forces larger groups.
-  const int q_top = q;
-  for (bool c10 = true;; c10 = false) {
-    q = q_top;
-    while (q > 1 && hard_block_lds(ds.nf, s, q, ds.nc, c10) > budget) q = (q + 1) / 2;
-    while (q > q_floor && ((n_sets + q - 1) / q) * tiles < target) q = (q + 1) / 2;
-    // equal chunks (a short last chunk leaves its blocks underused)
-    const int chunks = (std::max<int32_t>(n_sets, 1) + q - 1) / q;
-    *Q = (std::max<int32_t>(n_sets, 1) + chunks - 1) / chunks;
-    // Single-tile groups (measured fastest: larger groups leave a partly
-    // filled last round of blocks), unless the grid would exceed the launch
-    // limit; then the fewest tiles per group that fit it.
-    int tg = 1;
-    while (tg < kMaxTilesPerBlock && hard_block_count(ds, *Q, n_sets, tg) > kMaxHardBlocks) ++tg;
-    *TG = tg;
-    if (!c10 || hard_c10(tg)) break;
-  }
+  *Q = q;
+  while (*TG < kMaxTilesPerBlock && hard_block_count(ds, q, n_sets, *TG) > kMaxHardBlocks) ++*TG;
 }
 
 }  // namespace
