@@ -505,6 +505,12 @@ static aerl_status eval_common(aerl_ctx *ctx, int32_t dataset_id, int32_t pop_id
   h.correct = correct;
   h.confusion = confusion;
   if (S == 0) {
+    const HardTablePlan table = plan_hard_table(ds, pop.n_sets, ctx->n_cu);
+    if (table.Q) {
+      AERL_HIP(ctx, hipSetDevice(ctx->device));
+      AERL_HIP(ctx, launch_hard_table(h, table, stream));
+      return AERL_OK;
+    }
     hard_config(ds, pop.n_sets, ctx->n_cu, &h.samples_per_lane, &h.sets_per_chunk, &h.tiles_per_group);
   } else {
     if (S != 1 && S != 2 && S != 4) return fail(ctx, AERL_EINVAL, "samples_per_lane %d not in {1,2,4}", S);

@@ -162,6 +162,156 @@ __global__ __launch_bounds__(kReduceBlock) void k_hard_reduce(
   emit();
 }
 
+struct HardTableArgs {
+  const float *x_fm;
+  int64_t n_pad;
+  int32_t n_tiles, nf, nc;
+  const int32_t *tile_info;
+  const int4 *sets;
+  const uint4 *conds;
+  const uint4 *heads;
+  int32_t n_sets, Q;
+  int32_t *correct;
+  int32_t *confusion;
+};
+
+// A table that fits one block's LDS: block b evaluates rule sets [b*Q,
+// b*Q + Q) on all of it.  The table is staged once, with each feature's
+// extremes per tile reduced from the registers that carry it; then a wave
+// takes one (rule set, layout tile) after the other, the next one's set
+// record and head entries under way during the walk.  A set's confusion
+// counts are complete in its block, so they are stored, not added: one launch
+// instead of two fills and the evaluation.  Such launches are bound by
+// latency, stage after stage: of 6.4 us on 569 x 30 with 100 sets, the launch
+// takes 2.3, the staging 1.6 (its vector instructions count as much as its
+// loads: with a division per row and 64 or 128 samples per row 6 and 4.5) and
+// the walk 2.4.  A call whose outputs are allocated with it takes 10.1 us there,
+// most of it the host's, where the path above takes 16.6.
+template <bool CAT>
+__global__ __launch_bounds__(kHardBlock) void k_hard_table(const HardTableArgs a) {
+  extern __shared__ __align__(16) float smem[];
+  constexpr int S = 4, kWaves = kHardBlock / 64;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int ncc = hard_counters_per_set(a.nc);
+  const int set0 = blockIdx.x * a.Q;
+  const int Q = min(a.Q, a.n_sets - set0);
+  const int rows = a.n_tiles * a.nf;
+  float *xs = smem;                                              // [n_tiles][nf][AERL_TILE]
+  float *ext = xs + (size_t)rows * AERL_TILE;                    // [n_tiles][nf][max, -min]
+  int32_t *cnt = reinterpret_cast<int32_t *>(ext + 2 * rows);    // [Q][label][class]
+  int32_t *n_label = cnt + a.Q * a.nc * a.nc;                    // [nc]
+
+  int4 s4 = make_int4(0, 0, 0, 0);
+  uint4 head = make_uint4(0, 0, 0, 0);
+  const int n_items = Q * a.n_tiles;
+  auto request = [&](int i) {
+    s4 = ldc(a.sets, set0 + i / a.n_tiles);
+    const int nh = s4.y >> 16;
+    if (nh >= 1 && nh <= kMaxHeads) head = a.heads[s4.x + min(lane, nh - 1)];
+  };
+  if (wave < n_items) request(wave);
+
+  for (int i = threadIdx.x; i < Q * a.nc * a.nc; i += kHardBlock) cnt[i] = 0;
+  if ((int)threadIdx.x < a.nc) n_label[threadIdx.x] = 0;
+  // 16 lanes per row (one feature of one tile), eight loads under way per
+  // lane; a lane's next row is 64 on
+  const int col = threadIdx.x & 15;
+  constexpr int kStep = kHardBlock / 16, kBatch = 2;
+  const int step_t = kStep / a.nf, step_f = kStep - step_t * a.nf;
+  const uint32_t n_pad = (uint32_t)a.n_pad;
+  int r = threadIdx.x >> 4;
+  int t = r / a.nf, f = r - t * a.nf;
+  while (r < rows) {
+    f4v v[kBatch][S];
+    int valid[kBatch];
+    const int r0 = r;
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      if (r < rows) {
+        const f4v *src =
+            reinterpret_cast<const f4v *>(a.x_fm + ((uint32_t)f * n_pad + (uint32_t)(t * AERL_TILE))) + col;
+#pragma unroll
+        for (int j = 0; j < S; ++j) v[k][j] = src[16 * j];
+        valid[k] = a.tile_info[t] >> 8;
+      }
+      r += kStep;
+      t += step_t;
+      f += step_f;
+      if (f >= a.nf) {
+        f -= a.nf;
+        ++t;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      const int rk = r0 + k * kStep;
+      if (rk >= rows) break;
+      float hi = -INFINITY, lo = INFINITY;
+#pragma unroll
+      for (int j = 0; j < S; ++j) {
+        reinterpret_cast<f4v *>(xs)[rk * (AERL_TILE / 4) + 16 * j + col] = v[k][j];
+        widen(v[k][j], valid[k] - 64 * j - 4 * col, hi, lo);
+      }
+      hi = row_max(hi);
+      lo = row_max(-lo);
+      if (col == 0) *reinterpret_cast<float2 *>(ext + 2 * rk) = make_float2(hi, lo);
+    }
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < a.n_tiles) {
+    const int info = a.tile_info[threadIdx.x];
+    atomicAdd(&n_label[info & 0xff], info >> 8);
+  }
+  const uint32_t lds_lane =
+      (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) float *)xs + (uint32_t)lane * (4u * S);
+  for (int i = wave; i < n_items; i += kWaves) {
+    const int q = i / a.n_tiles, wt = i - q * a.n_tiles;
+    const int4 set = s4;
+    const uint4 h = head;
+    if (i + kWaves < n_items) request(i + kWaves);
+    const int info = ldc(a.tile_info, wt);
+    const int valid = info >> 8;
+    uint64_t vm[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) vm[s] = ballot(lane * S + s < valid);
+    const int nh = set.y >> 16;
+    const uint32_t base = lds_lane + (uint32_t)(wt * a.nf) * (4u * AERL_TILE);
+    int acc;
+    if (nh >= 1 && nh <= kMaxHeads) {
+      // lane j: rule j; table[e] < t' when no sample of the tile passes
+      const char *tb = reinterpret_cast<const char *>(ext + 2 * wt * a.nf);
+      const float e1 = *reinterpret_cast<const float *>(tb + (h.x >> kHeadExtShift));
+      const float e2 = *reinterpret_cast<const float *>(tb + h.z);
+      const uint64_t rules = ~0ull >> (64 - nh);
+      const uint64_t mk = (ballot(!(e1 < __uint_as_float(h.y))) &
+                           ballot(!(e2 < __uint_as_float(h.w))) & rules) |
+                          (1ull << (nh - 1));
+      acc = eval_set_count<S, true, CAT>(base, lane, set, a.conds, vm, mk, h.x & kHeadOffMask);
+    } else {
+      acc = eval_set_count<S, false, CAT>(base, lane, set, a.conds, vm);
+    }
+    if (lane < ncc) atomicAdd(&cnt[(q * a.nc + (info & 0xff)) * a.nc + lane], acc);
+  }
+  __syncthreads();
+  // the last class gets what the others leave of a region's samples
+  for (int i = threadIdx.x; i < Q * a.nc; i += kHardBlock) {
+    int rest = n_label[i % a.nc];
+    for (int c = 0; c < ncc; ++c) rest -= cnt[i * a.nc + c];
+    cnt[i * a.nc + ncc] = rest;
+  }
+  __syncthreads();
+  if (a.confusion) {
+    int32_t *out = a.confusion + (int64_t)set0 * a.nc * a.nc;
+    for (int i = threadIdx.x; i < Q * a.nc * a.nc; i += kHardBlock) out[i] = cnt[i];
+  }
+  for (int q = threadIdx.x; q < Q; q += kHardBlock) {
+    int hits = 0;
+    for (int c = 0; c < a.nc; ++c) hits += cnt[(q * a.nc + c) * a.nc + c];
+    a.correct[set0 + q] = hits;
+  }
+}
+
 // Prediction for one rule set over row-major rows, 64 S rows per block.
 template <int S>
 __global__ __launch_bounds__(kPredictBlock) void k_predict(const float *__restrict__ rows, int64_t n,
@@ -234,6 +384,33 @@ hipError_t launch_hard_eval(const HardLaunch &h, hipStream_t st) {
     case 1: return hard_dispatch<1>(a, grid, lds, pop.n_cat > 0, c10, st);
     default: return hipErrorInvalidValue;
   }
+}
+
+HardTablePlan plan_hard_table(const DatasetRec &ds, int32_t n_sets, int n_cu) {
+  HardTablePlan p{};
+  if (ds.n_tiles < 1 || n_sets < 1) return p;
+  const int64_t Q = ((int64_t)n_sets + n_cu - 1) / n_cu;  // one block per CU
+  if (ds.n_tiles > kHardTableVisits || Q * ds.n_tiles > kHardTableVisits) return p;
+  const size_t lds = (size_t)ds.n_tiles * ds.nf * (4 * AERL_TILE + 8) +
+                     sizeof(int32_t) * ((size_t)Q * ds.nc * ds.nc + ds.nc);
+  if (lds > kDynLdsMax) return p;
+  p.Q = (int)Q;
+  p.lds = lds;
+  return p;
+}
+
+hipError_t launch_hard_table(const HardLaunch &h, const HardTablePlan &p, hipStream_t st) {
+  const DatasetRec &ds = *h.ds;
+  const PopRec &pop = *h.pop;
+  if (p.Q < 1 || p.lds > kDynLdsMax || ds.n_tiles < 1 || h.set_begin != 0) return hipErrorInvalidValue;
+  const HardTableArgs a{ds.x_fm,    ds.n_pad,  (int32_t)ds.n_tiles, ds.nf, ds.nc,     ds.tile_info, pop.sets,
+                        pop.hconds, pop.heads, h.set_count,         p.Q,   h.correct, h.confusion};
+  const dim3 grid((unsigned)((h.set_count + p.Q - 1) / p.Q));
+  if (pop.n_cat > 0)
+    hipLaunchKernelGGL(k_hard_table<true>, grid, dim3(kHardBlock), p.lds, st, a);
+  else
+    hipLaunchKernelGGL(k_hard_table<false>, grid, dim3(kHardBlock), p.lds, st, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_hard_reduce(const HardLaunch &h, int n_cu, hipStream_t st) {

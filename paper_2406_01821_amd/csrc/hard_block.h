@@ -18,6 +18,29 @@ namespace aerl {
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 
+// Largest v of a DPP row's 16 lanes (all of them or none active), in each.
+template <int CTRL>
+__device__ __forceinline__ float dpp_max(float v) {
+  const int b = __float_as_int(v);
+  return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(b, b, CTRL, 0xf, 0xf, false)));
+}
+__device__ __forceinline__ float row_max(float v) {
+  v = dpp_max<0xb1>(v);     // lane ^ 1
+  v = dpp_max<0x4e>(v);     // lane ^ 2
+  v = dpp_max<0x141>(v);    // 7 - lane in each half row
+  return dpp_max<0x140>(v); // 15 - lane
+}
+
+// Largest and smallest of a DPP row's samples of one feature: lane `col` of
+// the 16 holds four consecutive ones in v, `left` of them real (at least one
+// of a lane's is where left > 0; the others repeat the first).
+__device__ __forceinline__ void widen(f4v v, int left, float &hi, float &lo) {
+  if (left <= 0) return;
+  const float e1 = left > 1 ? v[1] : v[0], e2 = left > 2 ? v[2] : v[0], e3 = left > 3 ? v[3] : v[0];
+  hi = fmaxf(fmaxf(hi, fmaxf(v[0], e1)), fmaxf(e2, e3));
+  lo = fminf(fminf(lo, fminf(v[0], e1)), fminf(e2, e3));
+}
+
 struct HardTask {
   const float *x_fm;
   int64_t n_pad;

@@ -217,6 +217,20 @@ hipError_t launch_hard_eval(const HardLaunch &h, hipStream_t s);
 // Sums h.part over the tiles of each class region into h.correct and
 // h.confusion (which must be zeroed), about two workgroups per CU.
 hipError_t launch_hard_reduce(const HardLaunch &h, int n_cu, hipStream_t s);
+// A table small enough for one block's LDS: one launch whose blocks each
+// evaluate Q rule sets on all of it (Q = 0: use the path above).  With up to
+// 80 (rule set, layout tile) pairs per block, five per wave, it is the faster
+// one over 2 to 28 tiles: 1 to 8 pairs 8 against 14 to 17 us, 60 pairs 18
+// against 23, 80 pairs 20 against 23; at 110 to 160 pairs the paths meet (31
+// against 30 us), and past that the redundant staging and the single round
+// of blocks lose to them (240 pairs 37 against 30 us).
+constexpr int kHardTableVisits = 80;
+struct HardTablePlan {
+  int Q;
+  size_t lds;
+};
+HardTablePlan plan_hard_table(const DatasetRec &ds, int32_t n_sets, int n_cu);
+hipError_t launch_hard_table(const HardLaunch &h, const HardTablePlan &p, hipStream_t s);
 // Per-tile counter buffers the plain hard path uses: for launches of at
 // least 4 Mi (tile, rule set) pairs (smaller ones flush per block, without
 // a second kernel) and at most 512 MiB of counter words (larger ones flush
