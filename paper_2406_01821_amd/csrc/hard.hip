@@ -48,7 +48,7 @@ struct HardArgs {
 // out of the other instantiation, which keeps the common walk's code tight).
 // C10: single-tile groups (10-bit LDS counters).
 template <int S, bool CAT, bool C10>
-__global__ __launch_bounds__(kHardBlock) AERL_HARD_SGPR_CAP void k_hard(const HardArgs a) {
+__global__ __launch_bounds__(kHardBlock, 8) AERL_HARD_SGPR_CAP void k_hard(const HardArgs a) {
   extern __shared__ __align__(16) float smem[];
   __shared__ int32_t sh[2];
   // Which class region and which tiles this block covers (uniform loop).

@@ -10,9 +10,9 @@
 namespace aerl {
 
 // Kernels running hard_block with 1024-thread blocks: two such blocks share a
-// CU (eight waves per SIMD) only when a wave holds at most 80 SGPRs; measured
-// on gfx950, 82 already leaves room for one block.  The cap makes the
-// compiler keep within it (spilling a few loop-invariant values to VGPR lanes
+// CU (eight waves per SIMD) only when a wave holds at most 64 VGPRs and 80
+// SGPRs; measured on gfx950, 82 already leave room for one block.  This cap
+// and eight waves per SIMD in the launch bounds make the compiler keep within them (spilling a few loop-invariant values to VGPR lanes
 // outside the rule-set loop); the asm walk's fixed quads s[64:71] lie below it.
 #define AERL_HARD_SGPR_CAP __attribute__((amdgpu_num_sgpr(80)))
 
@@ -83,6 +83,7 @@ __device__ __forceinline__ void hard_block(const HardTask &t, float *smem, int32
   int32_t *next_q = sh;
   constexpr int TS = 64 * S;           // samples per wave tile
   constexpr int WPT = AERL_TILE / TS;  // wave tiles per layout tile
+  constexpr int kBatch = S == 1 ? 2 : 1;     // features of which a lane loads at once
   float *xs = smem;                                                    // [nf][TS]
   float *ext = smem + (size_t)t.nf * TS;                               // [nf][max, -min]
   const int ncc = hard_counters_per_set(t.nc);                        // counted classes
@@ -96,51 +97,54 @@ __device__ __forceinline__ void hard_block(const HardTask &t, float *smem, int32
   for (int i = threadIdx.x; i < (int)(hard_counter_bytes(t.Q, t.nc, C10) / 4); i += blockDim.x)
     cnt32[i] = 0u;
   if (threadIdx.x == 0) sh[1] = 0;
-  const int n4 = t.nf * (TS / 4);
-  const float4 *src = reinterpret_cast<const float4 *>(t.x_fm);
-  float4 *dst = reinterpret_cast<float4 *>(xs);
-  const int64_t row4 = t.n_pad / 4;
+  const int col = threadIdx.x & 15;
   const uint32_t lds_lane =
       (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) float *)xs + (uint32_t)lane * (4u * S);
   for (int64_t wt = (int64_t)t.tile_lo * WPT; wt < (int64_t)t.tile_hi * WPT; ++wt) {
-    __syncthreads();  // everyone is done with the previous tile
-    const int64_t base4 = wt * (TS / 4);
-    for (int i = threadIdx.x; i < n4; i += blockDim.x) {
-      const int f = i / (TS / 4), k = i % (TS / 4);
-      // streamed once per block: a non-temporal load keeps it from pushing
-      // the rule records out of the L2
-      reinterpret_cast<f4v *>(dst)[i] =
-          __builtin_nontemporal_load(reinterpret_cast<const f4v *>(src + (int64_t)f * row4 + base4 + k));
-    }
-    if (threadIdx.x == 0) *next_q = 0;
-    __syncthreads();
     const int info = ldc(t.tile_info, wt / WPT);
     const int valid = min(max((info >> 8) - (int)(wt % WPT) * TS, 0), TS);
+    if (valid == 0) continue;  // an empty wave tile (S < 4 at a region's end)
     uint64_t vm[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) vm[s] = ballot(lane * S + s < valid);
-    if (valid == 0) continue;  // an empty wave tile (S < 4 at a region's end)
-    if (threadIdx.x == 0) sh[1] += valid;
-    // largest and negated smallest value of each feature over the valid
-    // samples: 16 threads per feature
-    for (int f0 = 0; f0 < t.nf; f0 += 64) {
-      const int f = f0 + (threadIdx.x >> 4), part = threadIdx.x & 15;
-      float hi = -INFINITY, lo = INFINITY;
-      if (f < t.nf) {
-        for (int i = part; i < valid; i += 16) {
-          const float v = xs[f * TS + i];
-          hi = fmaxf(hi, v);
-          lo = fminf(lo, v);
+    __syncthreads();  // everyone is done with the previous tile
+    // 16 lanes per feature, whose extremes come from the registers that carry
+    // the tile (a pass of its own over LDS, with 4-way bank conflicts and one
+    // more barrier, made launches of one tile per block 2 to 8% longer: 50 021
+    // x 97 x 377 sets 70.5 us against 67.5 now, 24 runs in a batch 694 against
+    // 662); a lane's next feature is blockDim.x / 16 on.  More loads under way
+    // per lane (8) push k_hard_batch past 64 VGPRs.  Streamed once per block:
+    // non-temporal loads keep the tile from pushing the rule records out of
+    // the L2.
+    const int step = blockDim.x >> 4;
+    for (int f0 = threadIdx.x >> 4; f0 < t.nf; f0 += kBatch * step) {
+      f4v v[kBatch][S];
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) {
+        const int f = f0 + k * step;
+        if (f >= t.nf) break;
+        const f4v *src = reinterpret_cast<const f4v *>(t.x_fm + (int64_t)f * t.n_pad + wt * TS) + col;
+#pragma unroll
+        for (int j = 0; j < S; ++j) v[k][j] = __builtin_nontemporal_load(src + 16 * j);
+      }
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) {
+        const int f = f0 + k * step;
+        if (f >= t.nf) break;
+        float hi = -INFINITY, lo = INFINITY;
+#pragma unroll
+        for (int j = 0; j < S; ++j) {
+          reinterpret_cast<f4v *>(xs)[f * (TS / 4) + 16 * j + col] = v[k][j];
+          widen(v[k][j], valid - 64 * j - 4 * col, hi, lo);
         }
+        hi = row_max(hi);
+        lo = row_max(-lo);
+        if (col == 0) *reinterpret_cast<float2 *>(ext + 2 * f) = make_float2(hi, lo);
       }
-      for (int d = 1; d < 16; d <<= 1) {
-        hi = fmaxf(hi, __shfl_xor(hi, d));
-        lo = fminf(lo, __shfl_xor(lo, d));
-      }
-      if (f < t.nf && part == 0) {
-        ext[2 * f] = hi;
-        ext[2 * f + 1] = -lo;
-      }
+    }
+    if (threadIdx.x == 0) {
+      *next_q = 0;
+      sh[1] += valid;
     }
     __syncthreads();
     for (;;) {

@@ -26,7 +26,7 @@ __global__ void k_batch_zero(const BatchZero *__restrict__ z, int32_t n_z, int32
 
 // CAT: some item has categorical conditions.
 template <bool CAT>
-__global__ __launch_bounds__(kBatchBlock) AERL_HARD_SGPR_CAP void k_hard_batch(
+__global__ __launch_bounds__(kBatchBlock, 8) AERL_HARD_SGPR_CAP void k_hard_batch(
     const BatchItem *__restrict__ items, const BatchTask *__restrict__ tasks, int32_t n_tasks,
     int32_t *__restrict__ counter) {
   extern __shared__ __align__(16) float smem[];
