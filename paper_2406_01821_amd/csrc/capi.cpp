@@ -226,7 +226,14 @@ aerl_status pack_staged(aerl_ctx *ctx, const aerl_population *pop, int32_t nf, i
     return fail(ctx, AERL_ENOMEM, "ws or staging holds less than the %zu bytes needed", L.total);
   PopRec rec;
   pack_population_image(pop, nf, nc, n_rules, n_conds, staging, &rec);
-  AERL_HIP(ctx, hipMemcpyAsync(ws, staging, L.total, hipMemcpyHostToDevice, stream));
+  // A small image is read from the pinned staging by a kernel, which starts
+  // sooner than a copy engine: 91 -> 86 us per generation of 100 rule sets (75
+  // KB); with 1000 (750 KB) both take 638.
+  constexpr size_t kKernelCopyBytes = 256 << 10;
+  if (L.total <= kKernelCopyBytes)
+    AERL_HIP(ctx, launch_copy16(ws, staging, (int64_t)(L.total / 16), stream));
+  else
+    AERL_HIP(ctx, hipMemcpyAsync(ws, staging, L.total, hipMemcpyHostToDevice, stream));
   set_device_views(rec, L, ws);
   const int32_t id = ctx->next_id++;
   ctx->pops[id] = rec;  // staging is the caller's: nothing to free on release

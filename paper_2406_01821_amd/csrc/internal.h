@@ -196,6 +196,8 @@ namespace aerl {
 // ------------------------------------------------------------ kernel launchers
 // All return hipSuccess or the first HIP error.
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
+// Copy of n 16-byte words, aligned, from pinned host memory or the device.
+hipError_t launch_copy16(void *dst, const void *src, int64_t n, hipStream_t s);
 
 struct HardLaunch {
   const DatasetRec *ds;

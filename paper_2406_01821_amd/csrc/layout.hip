@@ -27,6 +27,11 @@ __global__ void k_fill_i32(int32_t *__restrict__ p, int64_t n, int32_t v) {
   for (; i < n; i += stride) p[i] = v;
 }
 
+__global__ void k_copy16(uint4 *__restrict__ dst, const uint4 *__restrict__ src, int64_t n) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += stride) dst[i] = src[i];
+}
+
 // counts[c][g]: samples of class c among rows [g*R, (g+1)*R); c = nc: labels
 // outside [0, nc).  R is a power of two, 32..256.
 constexpr int kCountBlock = 256, kCountRows = 1024, kCountGroups = kCountRows / 32;
@@ -344,6 +349,15 @@ hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s) {
   int64_t blocks = (n + 255) / 256;
   if (blocks > 4096) blocks = 4096;
   hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)blocks), dim3(256), 0, s, p, n, v);
+  return hipGetLastError();
+}
+
+hipError_t launch_copy16(void *dst, const void *src, int64_t n, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  if (((uintptr_t)dst | (uintptr_t)src) & 15) return hipErrorInvalidValue;
+  const int64_t blocks = std::min<int64_t>((n + 255) / 256, 512);
+  hipLaunchKernelGGL(k_copy16, dim3((unsigned)blocks), dim3(256), 0, s, static_cast<uint4 *>(dst),
+                     static_cast<const uint4 *>(src), n);
   return hipGetLastError();
 }
 
