@@ -221,7 +221,9 @@ aerl_status aerl_release_population(aerl_ctx *ctx, int32_t pop_id);
  * the call keeps those counts in a device buffer the context owns
  * (allocated or grown on the first call that needs more, freed by
  * aerl_destroy); calls that use it run one after another, also across
- * streams.  Errors:
+ * streams.  A table whose padded tiles fit one workgroup's LDS is evaluated
+ * in one launch without that buffer, while a workgroup gets at most 80
+ * (256-sample tile, rule set) pairs.  Errors:
  * AERL_ENOENT, AERL_EINVAL (feature count or class count of the population
  * and dataset differ, NULL correct), AERL_EDEVICE. */
 aerl_status aerl_eval_population(aerl_ctx *ctx, int32_t dataset_id, int32_t pop_id,
@@ -230,7 +232,8 @@ aerl_status aerl_eval_population(aerl_ctx *ctx, int32_t dataset_id, int32_t pop_
 /* Launch configuration aerl_eval_population picks for a dataset with the
  * given per-class sample counts (class_count[n_classes]) and a population of
  * n_sets rule sets on a GPU with n_cu compute units.  Pure host arithmetic,
- * the same planner the call runs.
+ * the same planner the call runs (for a table that the call evaluates in
+ * one workgroup's LDS: the launch it would take otherwise).
  *   samples_per_lane, sets_per_chunk, tiles_per_group  as in
  *                    aerl_eval_population_cfg
  *   workgroups       one per (chunk of rule sets, group of tiles), in a
@@ -287,8 +290,9 @@ typedef struct {
  * KiB (an item takes 4, 2 or 1 samples per lane, the most whose 64-lane
  * tile of all its features fits the budget; above 80 only one block fits a
  * CU).  0 in a field asks for the library's choice (the tuned one when
- * aerl_autotune has seen a batch of this shape, else 512 sets, 1 tile,
- * 64 KiB). */
+ * aerl_autotune has seen a batch of this shape, else the cheapest by
+ * estimate of 32 to 512 sets by 1 or 2 tiles at 64 KiB, with 512 sets by 1
+ * tile where the workspace holds only that). */
 typedef struct {
   int32_t sets_per_task;
   int32_t tiles_per_task;
@@ -461,7 +465,7 @@ aerl_status aerl_soft_forward(aerl_ctx *ctx, int32_t dataset_id, int32_t pop_id,
  * theta entries of kind-1 conditions are written as 0).  The adjoint
  * recomputes every sigmoid instead of storing activations.  dloss is
  * device fp32 [n_sets]; ws holds at least backward_bytes.  Deterministic.
- * Rule sets of up to 32 rules run with the per-rule state in per-lane
+ * Rule sets of up to 64 rules run with the per-rule state in per-lane
  * memory; longer ones keep it in LDS with fewer waves per workgroup as they
  * grow, which bounds them (about 300 rules with few features).  Errors:
  * AERL_ENOENT, AERL_EINVAL (also: rule sets too long for the adjoint

@@ -279,9 +279,11 @@ std::array<int32_t, 3> default_split(const std::vector<ItemView> &v, int n_cu, c
 }
 
 // The caller's split, with zero fields taken from the tuned table for this
-// batch shape or the defaults.
+// batch shape or the planned default.  *plain, when given: the split with 512
+// sets by one tile for the fields that neither gives, whose workspace a caller
+// may have instead.
 aerl_status resolve_split(aerl_ctx *ctx, const std::vector<ItemView> &v, const aerl_batch_cfg *cfg,
-                          BatchSplit *sp) {
+                          BatchSplit *sp, BatchSplit *plain = nullptr) {
   load_tune_file(ctx);
   auto it = ctx->tuned.find(shape_key(v));
   const std::array<int32_t, 3> d =
@@ -295,6 +297,13 @@ aerl_status resolve_split(aerl_ctx *ctx, const std::vector<ItemView> &v, const a
   sp->Q = q;
   sp->TG = tg;
   sp->tile_budget = (size_t)kib * 1024;
+  if (plain) {
+    *plain = *sp;
+    if (it == ctx->tuned.end()) {
+      if (!cfg || cfg->sets_per_task == 0) plain->Q = 512;
+      if (!cfg || cfg->tiles_per_task == 0) plain->TG = 1;
+    }
+  }
   // work items are counted and indexed with int32 on the device
   int64_t tasks = 0;
   for (const auto &e : v) tasks += batch_task_count(*e.ds, e.pop->n_sets, *sp);
@@ -333,12 +342,14 @@ aerl_status aerl_batch_workspace_bytes(aerl_ctx *ctx, const aerl_batch_item *ite
   std::vector<ItemView> v;
   aerl_status st = gather(ctx, items, n_items, &v);
   if (st) return st;
-  BatchSplit sp;
-  st = resolve_split(ctx, v, cfg, &sp);
+  BatchSplit sp, plain;
+  st = resolve_split(ctx, v, cfg, &sp, &plain);
   if (st) return st;
   BatchTables b;
   build_batch_tables(sources(v), sp, &b);
   *bytes = b.bytes;
+  build_batch_tables(sources(v), plain, &b);
+  *bytes = std::max(*bytes, b.bytes);  // room for either split
   return AERL_OK;
 }
 
@@ -352,12 +363,13 @@ aerl_status aerl_batch_plan(aerl_ctx *ctx, const aerl_batch_item *items, int32_t
   std::vector<ItemView> v;
   aerl_status st = gather(ctx, items, n_items, &v);
   if (st) return st;
-  BatchSplit sp;
-  st = resolve_split(ctx, v, cfg, &sp);
+  BatchSplit sp, plain;
+  st = resolve_split(ctx, v, cfg, &sp, &plain);
   if (st) return st;
   AERL_HIP(ctx, hipSetDevice(ctx->device));
   BatchTables b;
   build_batch_tables(sources(v), sp, &b);
+  if (b.bytes > ws_bytes) build_batch_tables(sources(v), plain, &b);
   std::unique_ptr<BatchPlanRec, PlanDeleter> plan(new BatchPlanRec());
   st = upload_plan(ctx, b, ws, ws_bytes, stream, plan.get());
   if (st) return st;
