@@ -28,13 +28,13 @@ HBM_PEAK = 8.0e12                     # bytes/s
 
 
 # HBM bytes per launch of the hard-eval kernel on the 2^20 x 64, 4096-set
-# workload, from two rocprofv3 --pmc runs (FETCH_SIZE 271,703.5 KiB and
+# workload, from two rocprofv3 --pmc runs (FETCH_SIZE 271,780 KiB and
 # WRITE_SIZE 65,568.0 KiB per dispatch, scaled by what the counters read for a
 # plain 256 MiB copy: x1.99978 and x1.000), and the same for the kernel that
-# sums its per-tile counts (FETCH_SIZE 32,957.1 KiB, WRITE_SIZE 10,039.3 KiB).
+# sums its per-tile counts (FETCH_SIZE 32,979 KiB, WRITE_SIZE 10,039.3 KiB).
 # Valid only for the kernel, launch-configuration and record-layout sources
 # it was measured on.
-HARD_TRAFFIC = {"bytes": 6.2356e8, "reduce_bytes": 7.7812e7, "sources_sha256": "70e21aa2705ce79f"}
+HARD_TRAFFIC = {"bytes": 6.2369e8, "reduce_bytes": 7.7815e7, "sources_sha256": "2503dbf60df2442e"}
 HARD_SOURCES = ("hard.hip", "hard_block.h", "eval_core.h", "capi.cpp", "pack.cpp", "internal.h")
 
 
