@@ -145,16 +145,18 @@ __device__ __forceinline__ void cond_z_only(const SoftArgs &a, const float *xs, 
   }
 }
 
-// z2 of the N conditions j[] (forward pass): their records and x[f] rows are
-// requested together, so that their latencies overlap; the same arithmetic
-// as cond_z_only.  TONLY: threshold conditions only.
+// z2 of the conditions of N records recs[i[]], i < 64 (forward pass): the
+// records and x[f] rows are requested together, so that their latencies
+// overlap; the same arithmetic as cond_z_only.  The byte offsets from recs
+// take 32 bits, recs itself the 64 bits that a population of 2^28 conditions
+// and more needs.  TONLY: threshold conditions only.
 template <int S, bool TONLY, int N>
-__device__ __forceinline__ void cond_zn(const SoftArgs &a, const float *xs, int lane,
-                                        const int (&j)[N], float (&z)[N][S]) {
+__device__ __forceinline__ void cond_zn(const uint4 *recs, const float *xs, int lane,
+                                        const int (&i)[N], float (&z)[N][S]) {
   uint4 r[N];
   float xf[N][S];
 #pragma unroll
-  for (int k = 0; k < N; ++k) r[k] = ldc_at(a.crec, (uint32_t)j[k] * 16u);
+  for (int k = 0; k < N; ++k) r[k] = ldc_at(recs, (uint32_t)i[k] * 16u);
 #pragma unroll
   for (int k = 0; k < N; ++k) load_row<S>(xs, (r[k].x & 0xfffu) * 1024u, lane, xf[k]);
 #pragma unroll
@@ -183,15 +185,15 @@ __device__ __forceinline__ int pop_bit(uint64_t &m) {
   return i;
 }
 
-// Adds the conditions base + (set bits of act), in order, to ra.
+// Adds the conditions of recs[set bits of act], in order, to ra.
 template <int S, class Acc, bool TONLY, int N>
-__device__ __forceinline__ void add_n(const SoftArgs &a, const float *xs, int lane, int base,
-                                      uint64_t &act, Acc (&ra)[S]) {
-  int j[N];
+__device__ __forceinline__ void add_n(const uint4 *recs, const float *xs, int lane, uint64_t &act,
+                                      Acc (&ra)[S]) {
+  int i[N];
 #pragma unroll
-  for (int k = 0; k < N; ++k) j[k] = base + pop_bit(act);
+  for (int k = 0; k < N; ++k) i[k] = pop_bit(act);
   float z[N][S];
-  cond_zn<S, TONLY, N>(a, xs, lane, j, z);
+  cond_zn<S, TONLY, N>(recs, xs, lane, i, z);
 #pragma unroll
   for (int k = 0; k < N; ++k) {
 #pragma unroll
@@ -199,12 +201,12 @@ __device__ __forceinline__ void add_n(const SoftArgs &a, const float *xs, int la
   }
 }
 template <int S, class Acc, bool TONLY>
-__device__ __forceinline__ void add_conds(const SoftArgs &a, const float *xs, int lane, int base,
+__device__ __forceinline__ void add_conds(const uint4 *recs, const float *xs, int lane,
                                           uint64_t act, Acc (&ra)[S]) {
   int n = __builtin_popcountll(act);
-  for (; n >= 4; n -= 4) add_n<S, Acc, TONLY, 4>(a, xs, lane, base, act, ra);
-  if (n & 2) add_n<S, Acc, TONLY, 2>(a, xs, lane, base, act, ra);
-  if (n & 1) add_n<S, Acc, TONLY, 1>(a, xs, lane, base, act, ra);
+  for (; n >= 4; n -= 4) add_n<S, Acc, TONLY, 4>(recs, xs, lane, act, ra);
+  if (n & 2) add_n<S, Acc, TONLY, 2>(recs, xs, lane, act, ra);
+  if (n & 1) add_n<S, Acc, TONLY, 1>(recs, xs, lane, act, ra);
 }
 
 // Largest and smallest value of every feature over a staged tile's `valid`
@@ -336,7 +338,7 @@ template <int S, class Acc, bool TONLY>
 __device__ __forceinline__ void add_rule(const SoftArgs &a, const float *xs, int lane, int4 r,
                                          uint64_t act, Acc (&ra)[S]) {
   for (int b = 0;;) {
-    add_conds<S, Acc, TONLY>(a, xs, lane, r.x + b, act, ra);
+    add_conds<S, Acc, TONLY>(a.crec + (r.x + b), xs, lane, act, ra);
     b += 64;
     if (b >= r.y) break;
     act = low_bits(min(r.y - b, 64));
