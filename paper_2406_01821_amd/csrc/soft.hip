@@ -238,9 +238,8 @@ __device__ __forceinline__ void tile_extremes(const float *xs, int nf, int valid
 // with z2 < -t_dead for every sample of the tile, and `sat`, those with z2 >
 // t_sat for every sample.  Rounding is monotone, so z2 over the tile lies
 // between its values at the corners of the tile's feature extremes, formed
-// with the same operations; a corner that is NaN decides nothing (an
-// infinite parameter gives NaN inside the tile only where its corners have
-// opposite signs).  Categorical conditions decide nothing.
+// with the same operations (the parameters are those of set_regular, which
+// give no NaN).  Categorical conditions decide nothing.
 //
 // The thresholds are where the exponentials give exactly 0 (v_exp_f32
 // flushes below 2^-126), so what is left out would have added nothing:
@@ -268,8 +267,23 @@ struct Window {
   uint64_t dead, sat;
 };
 // Without classification: every condition decided neither way.
-__device__ __forceinline__ Window first_window(const SoftArgs &a) {
-  return {0, a.classify ? 0 : INT32_MAX, 0, 0};
+__device__ __forceinline__ Window first_window(bool on) { return {0, on ? 0 : INT32_MAX, 0, 0}; }
+
+// Whether every parameter of a rule set's conditions (ss, its soft record) is
+// one that z2 is not NaN for, on any sample and on the zeros of the padding:
+// not NaN, and but for a threshold not infinite.  Parameters arrive unchecked
+// (an optimizer run that diverges), and what NaN reaches has to show: a set
+// that fails this is swept in full, nothing of it left out as zero.
+__device__ __forceinline__ bool set_regular(const SoftArgs &a, int lane, int4 ss) {
+  bool odd = false;
+  for (int i = lane; i < ss.w; i += 64) {
+    const uint4 r = a.crec[ss.z + i];
+    const float c = __uint_as_float(r.y), rv = __uint_as_float(r.z), sinv = __uint_as_float(r.w);
+    const bool ok = __builtin_isfinite(c) && __builtin_isfinite(sinv) &&
+                    ((r.x & kSoftFF) ? __builtin_isfinite(rv) : rv == rv);
+    odd = odd || !(ok || (r.x & kSoftCat));
+  }
+  return ballot(odd) == 0;
 }
 template <bool TONLY>
 __device__ __forceinline__ void classify(const SoftArgs &a, const float2 *ext, int lane, int base,
@@ -401,7 +415,7 @@ __global__ __launch_bounds__(kSoftBlock) AERL_SOFT_SGPR_CAP void k_soft_fwd(cons
       const int4 ss = ldc(a.ssets, q0 + q);
       const int dflt = ldc(a.sets, q0 + q).z;
       const int set_end = ss.z + ss.w;
-      Window win = first_window(a);
+      Window win = first_window(a.classify && set_regular(a, lane, ss));
       float logpy[S], surv[S];
 #pragma unroll
       for (int s = 0; s < S; ++s) { logpy[s] = kNegInf; surv[s] = 0.0f; }
@@ -682,7 +696,8 @@ __global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_soft_bwd
       const int4 ss = ldc(a.ssets, q0 + q);
       const int dflt = ldc(a.sets, q0 + q).z;
       const int set_end = ss.z + ss.w;
-      Window win = first_window(a);
+      const bool regular = set_regular(a, lane, ss);
+      Window win = first_window(a.classify && regular);
       RuleState<S> L, B;
       float logpy[S], surv[S];
 #pragma unroll
@@ -734,7 +749,7 @@ __global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_soft_bwd
         float lk[S], bk[S], pre[S];
         L.get(k, lk);
         B.get(k, bk);
-        bool quiet = true;  // every term of the rule is 0 as computed
+        bool quiet = regular;  // every term of the rule is 0 as computed
 #pragma unroll
         for (int s = 0; s < S; ++s) {
           const float lm = hit ? log1mexp2(fminf(U[s], 0.0f)) : U[s];
@@ -1124,7 +1139,7 @@ __global__ __launch_bounds__(kSoftBlock) AERL_SOFT_SGPR_CAP void k_smax_fwd(cons
       const int4 ss = ldc(a.ssets, q0 + q);
       const int dflt = ldc(a.sets, q0 + q).z;
       const int set_end = ss.z + ss.w;
-      Window win = first_window(a);
+      Window win = first_window(a.classify && set_regular(a, lane, ss));
       float v[S][NC], surv[S];
 #pragma unroll
       for (int s = 0; s < S; ++s) {
@@ -1338,7 +1353,8 @@ __global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_smax_bwd
       const int4 ss = ldc(a.ssets, q0 + q);
       const int dflt = ldc(a.sets, q0 + q).z;
       const int set_end = ss.z + ss.w;
-      Window win = first_window(a);
+      const bool regular = set_regular(a, lane, ss);
+      Window win = first_window(a.classify && regular);
       RuleState<S> LA, LP, LB;
       float v[S][NC], surv[S];
 #pragma unroll
@@ -1387,7 +1403,7 @@ __global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_smax_bwd
         tail[s] = 0.0f;
       }
       // reverse sweep with the suffix of log2(1 - r_i) after k
-      win = first_window(a);
+      win = first_window(a.classify && regular);
       for (int k = ss.y - 1; k >= 0; --k) {
         const int4 r = ldc(a.rules, ss.x + k);
         uint64_t act;
@@ -1396,7 +1412,7 @@ __global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_smax_bwd
         float la[S], lp[S], drk[S];
         LA.get(k, la);
         LP.get(k, lp);
-        bool quiet = true;  // every term of the rule is 0 as computed
+        bool quiet = regular;  // every term of the rule is 0 as computed
 #pragma unroll
         for (int s = 0; s < S; ++s) {
           const float oth = lp[s] + tail[s];  // log2 prod_{i != k} (1 - r_i)
