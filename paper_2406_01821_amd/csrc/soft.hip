@@ -55,7 +55,7 @@ struct SoftArgs {
   double *part_loss;  // [n_groups][n_sets]
   float *part_grad;   // [n_groups][n_conds][2]
   int32_t n_conds;
-  int32_t classify;  // tiles classify the conditions (classify below)
+  int32_t classify;  // adjoints: tiles classify the conditions (classify below)
   int32_t region_tile0[AERL_MAX_CLASSES];
   int32_t region_tiles[AERL_MAX_CLASSES];
 };
@@ -145,11 +145,31 @@ __device__ __forceinline__ void cond_z_only(const SoftArgs &a, const float *xs, 
   }
 }
 
+// z2 of the condition of record r, x[f] read already.  TONLY: threshold
+// conditions only.
+template <int S, bool TONLY>
+__device__ __forceinline__ void record_z(uint4 r, const float *xs, int lane, const float (&xf)[S],
+                                         float (&z)[S]) {
+  const float c = __uint_as_float(r.y), rv = __uint_as_float(r.z), sinv = __uint_as_float(r.w);
+  if (!TONLY && (r.x & kSoftFF)) {
+    float xg[S];
+    load_row<S>(xs, ((r.x >> 12) & 0xfffu) * 1024u, lane, xg);
+#pragma unroll
+    for (int s = 0; s < S; ++s) z[s] = fmaf(c, xf[s], -(rv * xg[s])) * sinv;
+  } else if (!TONLY && (r.x & kSoftCat)) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) z[s] = cat_z(xf[s], r.y, r.z);
+  } else {
+#pragma unroll
+    for (int s = 0; s < S; ++s) z[s] = fmaf(c, xf[s], -rv) * sinv;
+  }
+}
+
 // z2 of the conditions of N records recs[i[]], i < 64 (forward pass): the
 // records and x[f] rows are requested together, so that their latencies
 // overlap; the same arithmetic as cond_z_only.  The byte offsets from recs
 // take 32 bits, recs itself the 64 bits that a population of 2^28 conditions
-// and more needs.  TONLY: threshold conditions only.
+// and more needs.
 template <int S, bool TONLY, int N>
 __device__ __forceinline__ void cond_zn(const uint4 *recs, const float *xs, int lane,
                                         const int (&i)[N], float (&z)[N][S]) {
@@ -160,22 +180,46 @@ __device__ __forceinline__ void cond_zn(const uint4 *recs, const float *xs, int 
 #pragma unroll
   for (int k = 0; k < N; ++k) load_row<S>(xs, (r[k].x & 0xfffu) * 1024u, lane, xf[k]);
 #pragma unroll
-  for (int k = 0; k < N; ++k) {
-    const uint32_t sc = r[k].x;
-    const float c = __uint_as_float(r[k].y), rv = __uint_as_float(r[k].z);
-    const float sinv = __uint_as_float(r[k].w);
-    if (!TONLY && (sc & kSoftFF)) {
-      float xg[S];
-      load_row<S>(xs, ((sc >> 12) & 0xfffu) * 1024u, lane, xg);
+  for (int k = 0; k < N; ++k) record_z<S, TONLY>(r[k], xs, lane, xf[k], z[k]);
+}
+
+// z2 of four consecutive conditions j .. j+3: their records in one 64-byte
+// scalar load; the same arithmetic as cond_z_only.
+template <int S, bool TONLY>
+__device__ __forceinline__ void cond_z4(const SoftArgs &a, const float *xs, int lane, int j,
+                                        float (&z)[4][S]) {
+  typedef uint32_t v16u __attribute__((ext_vector_type(16)));
+  typedef const __attribute__((address_space(4))) v16u *cptr;
+  const v16u r = *(cptr)(a.crec + j);
+  float xf[4][S];
 #pragma unroll
-      for (int s = 0; s < S; ++s) z[k][s] = fmaf(c, xf[k][s], -(rv * xg[s])) * sinv;
-    } else if (!TONLY && (sc & kSoftCat)) {
+  for (int k = 0; k < 4; ++k) load_row<S>(xs, (r[4 * k] & 0xfffu) * 1024u, lane, xf[k]);
 #pragma unroll
-      for (int s = 0; s < S; ++s) z[k][s] = cat_z(xf[k][s], r[k].y, r[k].z);
-    } else {
+  for (int k = 0; k < 4; ++k)
+    record_z<S, TONLY>(make_uint4(r[4 * k], r[4 * k + 1], r[4 * k + 2], r[4 * k + 3]), xs, lane, xf[k], z[k]);
+}
+
+// Adds all of a rule's conditions to ra, four at a time (the sweep of tables
+// that do not classify).
+template <int S, class Acc, bool TONLY>
+__device__ __forceinline__ void add_all(const SoftArgs &a, const float *xs, int lane, int4 r,
+                                        Acc (&ra)[S]) {
+  int j = r.x;
+  const int je = r.x + r.y;
+  for (; j + 4 <= je; j += 4) {
+    float z[4][S];
+    cond_z4<S, TONLY>(a, xs, lane, j, z);
 #pragma unroll
-      for (int s = 0; s < S; ++s) z[k][s] = fmaf(c, xf[k][s], -rv) * sinv;
+    for (int c = 0; c < 4; ++c) {
+#pragma unroll
+      for (int s = 0; s < S; ++s) (void)ra[s].add(z[c][s]);
     }
+  }
+  for (; j < je; ++j) {
+    float z[S];
+    cond_z_only<S>(a, xs, lane, j, z);
+#pragma unroll
+    for (int s = 0; s < S; ++s) (void)ra[s].add(z[s]);
   }
 }
 
@@ -375,13 +419,15 @@ constexpr int kSoftBlock = 512;
 #define AERL_SOFT_SGPR_CAP __attribute__((amdgpu_num_sgpr(80)))
 
 // ------------------------------------------------------------------ forward
-template <int S, class Acc, bool TONLY>
-__global__ __launch_bounds__(kSoftBlock) AERL_SOFT_SGPR_CAP void k_soft_fwd(const SoftArgs a) {
+// Body shared by the kernel that classifies a tile's conditions (CLS) and the
+// one that takes all of them (forward_classifies chooses).
+template <int S, class Acc, bool TONLY, bool CLS>
+__device__ __forceinline__ void soft_fwd(const SoftArgs a) {
   constexpr int TS = 64 * S, WPT = AERL_TILE / TS;
   extern __shared__ __align__(16) float smem[];
   float *xs = smem;
-  float2 *ext = reinterpret_cast<float2 *>(smem + (size_t)a.nf * TS);  // [nf]
-  double *acc = reinterpret_cast<double *>(ext + a.nf);                // [Q]
+  float2 *ext = reinterpret_cast<float2 *>(smem + (size_t)a.nf * TS);  // [nf] with CLS
+  double *acc = reinterpret_cast<double *>(ext + (CLS ? a.nf : 0));    // [Q]
   __shared__ int32_t next_q;
   const int lane = threadIdx.x & 63;
   int label, tile_lo, tile_hi;
@@ -404,8 +450,8 @@ __global__ __launch_bounds__(kSoftBlock) AERL_SOFT_SGPR_CAP void k_soft_fwd(cons
     __syncthreads();
     const int info = ldc(a.tile_info, wt / WPT);
     const int valid = min(max((info >> 8) - (int)(wt % WPT) * TS, 0), TS);
-    if (valid == 0) continue;  // an empty wave tile (S < 4 at a region's end)
-    if (a.classify) tile_extremes<TS>(xs, a.nf, valid, ext);
+    if (S < 4 && valid == 0) continue;  // an empty wave tile (S < 4 at a region's end)
+    if constexpr (CLS) tile_extremes<TS>(xs, a.nf, valid, ext);
     bool live[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) live[s] = lane * S + s < valid;
@@ -415,7 +461,8 @@ __global__ __launch_bounds__(kSoftBlock) AERL_SOFT_SGPR_CAP void k_soft_fwd(cons
       const int4 ss = ldc(a.ssets, q0 + q);
       const int dflt = ldc(a.sets, q0 + q).z;
       const int set_end = ss.z + ss.w;
-      Window win = first_window(a.classify && set_regular(a, lane, ss));
+      Window win;
+      if constexpr (CLS) win = first_window(set_regular(a, lane, ss));
       float logpy[S], surv[S];
 #pragma unroll
       for (int s = 0; s < S; ++s) { logpy[s] = kNegInf; surv[s] = 0.0f; }
@@ -424,10 +471,14 @@ __global__ __launch_bounds__(kSoftBlock) AERL_SOFT_SGPR_CAP void k_soft_fwd(cons
       for (int k = 0; k < ss.y; ++k) {
         const int4 r = r_next;
         r_next = ldc(a.rules, ss.x + min(k + 1, ss.y - 1));
-        uint64_t act;
-        if (!rule_live<TONLY>(a, ext, lane, r, set_end, kDeadLoss, Acc::kNoop, win, act)) continue;
         Acc ra[S];
-        add_rule<S, Acc, TONLY>(a, xs, lane, r, act, ra);
+        if constexpr (CLS) {
+          uint64_t act;
+          if (!rule_live<TONLY>(a, ext, lane, r, set_end, kDeadLoss, Acc::kNoop, win, act)) continue;
+          add_rule<S, Acc, TONLY>(a, xs, lane, r, act, ra);
+        } else {
+          add_all<S, Acc, TONLY>(a, xs, lane, r, ra);
+        }
         const bool hit = r.z == label;
 #pragma unroll
         for (int s = 0; s < S; ++s) {
@@ -450,6 +501,15 @@ __global__ __launch_bounds__(kSoftBlock) AERL_SOFT_SGPR_CAP void k_soft_fwd(cons
   __syncthreads();
   for (int i = threadIdx.x; i < Q; i += blockDim.x)
     a.part_loss[(int64_t)blockIdx.y * a.n_sets + q0 + i] = acc[i];
+}
+
+template <int S, class Acc, bool TONLY>
+__global__ __launch_bounds__(kSoftBlock) AERL_SOFT_SGPR_CAP void k_soft_fwd_cls(const SoftArgs a) {
+  soft_fwd<S, Acc, TONLY, true>(a);
+}
+template <int S, class Acc, bool TONLY>
+__global__ __launch_bounds__(kSoftBlock) void k_soft_fwd(const SoftArgs a) {
+  soft_fwd<S, Acc, TONLY, false>(a);
 }
 
 // Mean loss per rule set from the per-group partial sums: block b takes
@@ -815,15 +875,16 @@ __global__ void k_soft_bwd_final(const float *__restrict__ part, int32_t n_group
 struct SoftPlan {
   int S, Q, TG, n_groups;
   bool reg;   // backward: per-rule state in private memory, else in LDS
+  bool cls;   // forward: tiles classify the conditions
   int waves;  // LDS-state kernels: waves per block
   size_t lds;
 };
 
-// Tables of at least this many tiles classify conditions per tile.  On fewer,
-// a tile spans most of each column's range and little is decided: the adjoint
-// of 100 rule sets on 569 samples takes 46.0 us with and 45.0 us without it,
-// on 4000 samples 47.5 and 46.8 us (94 and 96 us with longer rule sets); on
-// 20,000 samples a forward pass takes 60 us with and 86 us without it.
+// Adjoints of tables of at least this many tiles classify conditions per tile.
+// On fewer, a tile spans most of each column's range and little is decided: the
+// adjoint of 100 rule sets on 569 samples takes 46.0 us with and 45.0 us
+// without it, on 4000 samples 47.5 and 46.8 us (94 and 96 us with longer rule
+// sets).
 constexpr int64_t kClassifyTiles = 16;
 
 // Feature tile and its extremes.
@@ -884,17 +945,42 @@ int sets_per_block(int n_sets, int64_t groups, int64_t target, int min_q) {
   return q;
 }
 
+// Whether a forward pass classifies.  Per tile it costs the extremes (a pass
+// over nf rows) and per rule set and 64 conditions a classification, and it
+// saves a share of the sweep that grows with the conditions of a rule (one out
+// of reach drops the rule).  Of 270 shapes timed both ways the line falls where
+// a launch has 600,000 (tile, condition) pairs (60,000 x 32, 40 rule sets of 8
+// x 4 conditions: 45 us, plain 55; 262,144 x 32 x 1024 of 16 x 4: 3.0 and 6.5
+// ms); on wider tables, whose tiles are half or a quarter as long for the same
+// extremes, only with enough rule sets per block (30,000 x 90 x 200 of 8-16 x
+// 2-5: 190 and 180 us).  Smaller launches gain on narrow tables alone (40,000 x
+// 60, 16 rule sets: 37 and 28 us; 20,011 x 45, 150 of 1-24 x 1-6: 98 and 104),
+// by rules of more than two conditions or many of them per staged value (23,741
+// x 38, 32 of 24 x 2: 52 and 49 us).  Rules of more than 64 conditions are
+// swept in full in any case.
+bool forward_classifies(const DatasetRec &ds, const PopRec &pop, int sets_per_block) {
+  if (ds.n_tiles < kClassifyTiles || pop.n_conds > 72LL * pop.n_rules) return false;
+  const double per_block = (double)sets_per_block * pop.n_conds / std::max(pop.n_sets, 1);
+  if ((double)ds.n_tiles * pop.n_conds >= 6e5) return ds.nf <= 64 || per_block >= 8.0 * ds.nf;
+  return ds.n_tiles >= 24 && ds.nf <= 52 && per_block >= 200 &&
+         (pop.n_conds >= 2.5 * pop.n_rules || per_block >= 12.0 * ds.nf);
+}
+
+// Forward tile and, with cls, its extremes.
+size_t fwd_tile_lds(int nf, int S, bool cls) { return cls ? tile_lds(nf, S) : (size_t)nf * 64 * S * 4; }
+
 SoftPlan plan_forward(const DatasetRec &ds, const PopRec &pop) {
   SoftPlan p{};
-  // four samples per lane while three blocks fit a CU (60,000 x 60, where two
-  // would: 611 us, with two samples per lane 560 us), then two while two fit
-  p.S = tile_lds(ds.nf, 4) <= kLdsPerCu / 3 ? 4 : 2;
-  while (p.S > 1 && (size_t)ds.nf * 256 * p.S > 64 * 1024) p.S >>= 1;
   p.Q = sets_per_block(pop.n_sets, count_groups(ds, 1), kFwdTargetBlocks, kSoftBlock / 64);
+  p.cls = forward_classifies(ds, pop, p.Q);
+  // four samples per lane; where tiles classify, while three blocks fit a CU
+  // (60,000 x 60, where two would: 611 us, with two samples per lane 560 us)
+  p.S = !p.cls || tile_lds(ds.nf, 4) <= kLdsPerCu / 3 ? 4 : 2;
+  while (p.S > 1 && (size_t)ds.nf * 256 * p.S > 64 * 1024) p.S >>= 1;
   p.TG = tiles_per_group(ds, (pop.n_sets + p.Q - 1) / p.Q, kFwdTargetBlocks,
                          (size_t)std::max(pop.n_sets, 1) * sizeof(double), kFwdPartMax);
   p.n_groups = (int)count_groups(ds, p.TG);
-  p.lds = tile_lds(ds.nf, p.S) + (size_t)p.Q * 8;
+  p.lds = fwd_tile_lds(ds.nf, p.S, p.cls) + (size_t)p.Q * 8;
   return p;
 }
 
@@ -960,12 +1046,20 @@ void fill_args(SoftArgs &a, const SoftLaunch &l, const SoftPlan &p) {
   }
 }
 
+template <int S, class Acc, bool TONLY>
+void launch_fwd_s(const SoftPlan &p, dim3 grid, hipStream_t st, const SoftArgs &a) {
+  if (p.cls)
+    hipLaunchKernelGGL((k_soft_fwd_cls<S, Acc, TONLY>), grid, dim3(kSoftBlock), p.lds, st, a);
+  else
+    hipLaunchKernelGGL((k_soft_fwd<S, Acc, TONLY>), grid, dim3(kSoftBlock), p.lds, st, a);
+}
+
 template <class Acc, bool TONLY>
 void launch_fwd(const SoftPlan &p, dim3 grid, hipStream_t st, const SoftArgs &a) {
   switch (p.S) {
-    case 4: hipLaunchKernelGGL((k_soft_fwd<4, Acc, TONLY>), grid, dim3(kSoftBlock), p.lds, st, a); break;
-    case 2: hipLaunchKernelGGL((k_soft_fwd<2, Acc, TONLY>), grid, dim3(kSoftBlock), p.lds, st, a); break;
-    default: hipLaunchKernelGGL((k_soft_fwd<1, Acc, TONLY>), grid, dim3(kSoftBlock), p.lds, st, a); break;
+    case 4: launch_fwd_s<4, Acc, TONLY>(p, grid, st, a); break;
+    case 2: launch_fwd_s<2, Acc, TONLY>(p, grid, st, a); break;
+    default: launch_fwd_s<1, Acc, TONLY>(p, grid, st, a); break;
   }
 }
 
@@ -1102,13 +1196,13 @@ __device__ __forceinline__ float smax_log2py(const float (&v)[NC], int nc, float
 
 constexpr int kSmaxBwdWaves = 4;
 
-template <int S, int NC, class Acc, bool TONLY>
-__global__ __launch_bounds__(kSoftBlock) AERL_SOFT_SGPR_CAP void k_smax_fwd(const SoftArgs a, float beta2) {
+template <int S, int NC, class Acc, bool TONLY, bool CLS>
+__device__ __forceinline__ void smax_fwd(const SoftArgs a, float beta2) {
   constexpr int TS = 64 * S, WPT = AERL_TILE / TS;
   extern __shared__ __align__(16) float smem[];
   float *xs = smem;
-  float2 *ext = reinterpret_cast<float2 *>(smem + (size_t)a.nf * TS);  // [nf]
-  double *acc = reinterpret_cast<double *>(ext + a.nf);                // [Q]
+  float2 *ext = reinterpret_cast<float2 *>(smem + (size_t)a.nf * TS);  // [nf] with CLS
+  double *acc = reinterpret_cast<double *>(ext + (CLS ? a.nf : 0));    // [Q]
   __shared__ int32_t next_q;
   const int lane = threadIdx.x & 63;
   int label, tile_lo, tile_hi;
@@ -1131,15 +1225,16 @@ __global__ __launch_bounds__(kSoftBlock) AERL_SOFT_SGPR_CAP void k_smax_fwd(cons
     __syncthreads();
     const int info = ldc(a.tile_info, wt / WPT);
     const int valid = min(max((info >> 8) - (int)(wt % WPT) * TS, 0), TS);
-    if (valid == 0) continue;  // an empty wave tile (S < 4 at a region's end)
-    if (a.classify) tile_extremes<TS>(xs, a.nf, valid, ext);
+    if (S < 4 && valid == 0) continue;  // an empty wave tile (S < 4 at a region's end)
+    if constexpr (CLS) tile_extremes<TS>(xs, a.nf, valid, ext);
     for (;;) {
       const int q = next_item(&next_q);
       if (q >= Q) break;
       const int4 ss = ldc(a.ssets, q0 + q);
       const int dflt = ldc(a.sets, q0 + q).z;
       const int set_end = ss.z + ss.w;
-      Window win = first_window(a.classify && set_regular(a, lane, ss));
+      Window win;
+      if constexpr (CLS) win = first_window(set_regular(a, lane, ss));
       float v[S][NC], surv[S];
 #pragma unroll
       for (int s = 0; s < S; ++s) {
@@ -1149,10 +1244,14 @@ __global__ __launch_bounds__(kSoftBlock) AERL_SOFT_SGPR_CAP void k_smax_fwd(cons
       }
       for (int k = 0; k < ss.y; ++k) {
         const int4 r = ldc(a.rules, ss.x + k);
-        uint64_t act;
-        if (!rule_live<TONLY>(a, ext, lane, r, set_end, kDeadProb, Acc::kNoop, win, act)) continue;
         Acc ra[S];
-        add_rule<S, Acc, TONLY>(a, xs, lane, r, act, ra);
+        if constexpr (CLS) {
+          uint64_t act;
+          if (!rule_live<TONLY>(a, ext, lane, r, set_end, kDeadProb, Acc::kNoop, win, act)) continue;
+          add_rule<S, Acc, TONLY>(a, xs, lane, r, act, ra);
+        } else {
+          add_all<S, Acc, TONLY>(a, xs, lane, r, ra);
+        }
 #pragma unroll
         for (int s = 0; s < S; ++s) {
           float a2, b2;
@@ -1176,6 +1275,16 @@ __global__ __launch_bounds__(kSoftBlock) AERL_SOFT_SGPR_CAP void k_smax_fwd(cons
   __syncthreads();
   for (int i = threadIdx.x; i < Q; i += blockDim.x)
     a.part_loss[(int64_t)blockIdx.y * a.n_sets + q0 + i] = acc[i];
+}
+
+template <int S, int NC, class Acc, bool TONLY>
+__global__ __launch_bounds__(kSoftBlock) AERL_SOFT_SGPR_CAP void k_smax_fwd_cls(const SoftArgs a,
+                                                                                 float beta2) {
+  smax_fwd<S, NC, Acc, TONLY, true>(a, beta2);
+}
+template <int S, int NC, class Acc, bool TONLY>
+__global__ __launch_bounds__(kSoftBlock) void k_smax_fwd(const SoftArgs a, float beta2) {
+  smax_fwd<S, NC, Acc, TONLY, false>(a, beta2);
 }
 
 template <int NC, class Acc>
@@ -1498,28 +1607,38 @@ SoftPlan plan_smax_backward(const DatasetRec &ds, const PopRec &pop) {
 // Same groups (and so the same workspace) as the first-firing forward.  Four
 // samples per lane up to four classes and while three blocks fit a CU
 // (20,011 x 45, 150 mixed rule sets: 94 us, with two samples 111 us; 60,000 x
-// 60, where two would fit: 576 and 517 us), else two, one where two and the
-// extremes do not fit.
+// 60, where two would fit: 576 and 517 us), but not in a plain sweep of rules
+// past the product form, whose registers would leave four waves per SIMD; else
+// two, one where two do not fit.
 SoftPlan plan_smax_forward(const DatasetRec &ds, const PopRec &pop) {
   SoftPlan p = plan_forward(ds, pop);
-  p.S = smax_nc(ds.nc) <= 4 && tile_lds(ds.nf, 4) <= kLdsPerCu / 3 ? 4 : 2;
-  if (tile_lds(ds.nf, p.S) + (size_t)p.Q * 8 > kDynLdsMax) p.S = 1;
-  p.lds = tile_lds(ds.nf, p.S) + (size_t)p.Q * 8;
+  const bool wide = p.cls || pop.max_rule_conds <= kProdMaxConds;
+  p.S = smax_nc(ds.nc) <= 4 && wide && fwd_tile_lds(ds.nf, 4, p.cls) <= kLdsPerCu / 3 ? 4 : 2;
+  if (fwd_tile_lds(ds.nf, p.S, p.cls) + (size_t)p.Q * 8 > kDynLdsMax) p.S = 1;
+  p.lds = fwd_tile_lds(ds.nf, p.S, p.cls) + (size_t)p.Q * 8;
   return p;
+}
+
+template <int S, int NC, class Acc, bool TONLY>
+void launch_smax_fwd_t(const SoftPlan &p, dim3 grid, hipStream_t st, const SoftArgs &a, float beta2) {
+  const dim3 b(kSoftBlock);
+  if (p.cls)
+    hipLaunchKernelGGL((k_smax_fwd_cls<S, NC, Acc, TONLY>), grid, b, p.lds, st, a, beta2);
+  else
+    hipLaunchKernelGGL((k_smax_fwd<S, NC, Acc, TONLY>), grid, b, p.lds, st, a, beta2);
 }
 
 template <int S, int NC>
 void launch_smax_fwd_s(const SoftPlan &p, dim3 grid, hipStream_t st, const SoftArgs &a, bool prod,
                        bool tonly, float beta2) {
-  const dim3 b(kSoftBlock);
   if (prod && tonly)
-    hipLaunchKernelGGL((k_smax_fwd<S, NC, RuleProd, true>), grid, b, p.lds, st, a, beta2);
+    launch_smax_fwd_t<S, NC, RuleProd, true>(p, grid, st, a, beta2);
   else if (prod)
-    hipLaunchKernelGGL((k_smax_fwd<S, NC, RuleProd, false>), grid, b, p.lds, st, a, beta2);
+    launch_smax_fwd_t<S, NC, RuleProd, false>(p, grid, st, a, beta2);
   else if (tonly)
-    hipLaunchKernelGGL((k_smax_fwd<S, NC, RuleAcc, true>), grid, b, p.lds, st, a, beta2);
+    launch_smax_fwd_t<S, NC, RuleAcc, true>(p, grid, st, a, beta2);
   else
-    hipLaunchKernelGGL((k_smax_fwd<S, NC, RuleAcc, false>), grid, b, p.lds, st, a, beta2);
+    launch_smax_fwd_t<S, NC, RuleAcc, false>(p, grid, st, a, beta2);
 }
 
 template <int NC>
