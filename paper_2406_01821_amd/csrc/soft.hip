@@ -419,8 +419,12 @@ constexpr int kSoftBlock = 512;
 #define AERL_SOFT_SGPR_CAP __attribute__((amdgpu_num_sgpr(80)))
 
 // ------------------------------------------------------------------ forward
-// Body shared by the kernel that classifies a tile's conditions (CLS) and the
-// one that takes all of them (forward_classifies chooses).
+// Bodies shared by the kernels that classify a tile's conditions (CLS) and
+// those that take all of them (forward_classifies chooses).  The classifying
+// ones are held to eight waves per SIMD, which their larger state would
+// leave: 64 VGPRs and 80 SGPRs (rules of more than 60 conditions would take
+// 88-109 VGPRs and four waves, the softmax head of 16 classes 91 and five).
+// The others fit by themselves and spill nothing.
 template <int S, class Acc, bool TONLY, bool CLS>
 __device__ __forceinline__ void soft_fwd(const SoftArgs a) {
   constexpr int TS = 64 * S, WPT = AERL_TILE / TS;
@@ -504,7 +508,7 @@ __device__ __forceinline__ void soft_fwd(const SoftArgs a) {
 }
 
 template <int S, class Acc, bool TONLY>
-__global__ __launch_bounds__(kSoftBlock) AERL_SOFT_SGPR_CAP void k_soft_fwd_cls(const SoftArgs a) {
+__global__ __launch_bounds__(kSoftBlock, 8) AERL_SOFT_SGPR_CAP void k_soft_fwd_cls(const SoftArgs a) {
   soft_fwd<S, Acc, TONLY, true>(a);
 }
 template <int S, class Acc, bool TONLY>
@@ -1278,7 +1282,7 @@ __device__ __forceinline__ void smax_fwd(const SoftArgs a, float beta2) {
 }
 
 template <int S, int NC, class Acc, bool TONLY>
-__global__ __launch_bounds__(kSoftBlock) AERL_SOFT_SGPR_CAP void k_smax_fwd_cls(const SoftArgs a,
+__global__ __launch_bounds__(kSoftBlock, 8) AERL_SOFT_SGPR_CAP void k_smax_fwd_cls(const SoftArgs a,
                                                                                  float beta2) {
   smax_fwd<S, NC, Acc, TONLY, true>(a, beta2);
 }
