@@ -318,15 +318,26 @@ __device__ __forceinline__ Window first_window(bool on) { return {0, on ? 0 : IN
 // not NaN, and but for a threshold not infinite.  Parameters arrive unchecked
 // (an optimizer run that diverges), and what NaN reaches has to show: a set
 // that fails this is swept in full, nothing of it left out as zero.
+// Four records per lane are requested at a time: a set of 1000 conditions
+// waits four times, not sixteen.
 __device__ __forceinline__ bool set_regular(const SoftArgs &a, int lane, int4 ss) {
   bool odd = false;
-  for (int i = lane; i < ss.w; i += 64) {
-    const uint4 r = a.crec[ss.z + i];
+  const uint4 *recs = a.crec + ss.z;
+  const auto look = [&](uint4 r) {
     const float c = __uint_as_float(r.y), rv = __uint_as_float(r.z), sinv = __uint_as_float(r.w);
     const bool ok = __builtin_isfinite(c) && __builtin_isfinite(sinv) &&
                     ((r.x & kSoftFF) ? __builtin_isfinite(rv) : rv == rv);
     odd = odd || !(ok || (r.x & kSoftCat));
+  };
+  int i = lane;
+  for (; i + 192 < ss.w; i += 256) {
+    uint4 r[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r[k] = recs[i + 64 * k];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) look(r[k]);
   }
+  for (; i < ss.w; i += 64) look(recs[i]);
   return ballot(odd) == 0;
 }
 template <bool TONLY>
@@ -644,20 +655,6 @@ __global__ __launch_bounds__(kBwdWaves * 64) void k_soft_bwd(const SoftArgs a) {
   }
 }
 
-// Adjoint for rule sets of at most kRegRules rules with S samples per lane:
-// the per-rule state kept between the two sweeps is l_k = a_k + (survival
-// before k) and log2(1 - r_k), in per-lane private memory (scratch, served by
-// the vector caches: only the rows of a set's own rules are touched, so the
-// bound costs nothing below it).  The reverse sweep recomputes every
-// condition once for its sigmoid(-z); only a rule of the label adds its
-// conditions up again, for the a_k of the U recurrence (the other rules' step
-// of it needs log2(1 - r_k) alone).  Per condition the S slots are summed in
-// the lane; two conditions' sums go over the wave in one reduction
-// (wave_totals4), and the lane that ends each adds it to the block's LDS
-// accumulators (one writer per rule set and tile).  Eight waves per SIMD (two
-// blocks per CU) at 64 VGPRs and 80 SGPRs: sets of up to 24 rules on 20,011 x
-// 45 take 234 us (520 us with two samples per lane, 124 VGPRs and one block
-// per CU), of 10-16 rules on 60,000 x 90 0.83 ms (1.39 ms likewise).
 // The reverse sweep over one rule's conditions, two at a time: their four
 // sums over the wave in one reduction (wave_totals4), added (negated when
 // neg) to the rule set's block accumulators accq by the lane that holds each
@@ -718,8 +715,22 @@ __device__ __forceinline__ void bwd_rule_conds(const SoftArgs &a, const float *x
 // still leaves 32 waves per CU.
 constexpr int kBwdRegBlock = 1024;
 
+// Adjoint for rule sets of at most kRegRules rules with S samples per lane:
+// the per-rule state kept between the two sweeps is l_k = a_k + (survival
+// before k) and log2(1 - r_k), in per-lane private memory (scratch, served by
+// the vector caches: only the rows of a set's own rules are touched; R, 16 or
+// 64, bounds what is reserved).  The reverse sweep recomputes every
+// condition once for its sigmoid(-z); only a rule of the label adds its
+// conditions up again, for the a_k of the U recurrence (the other rules' step
+// of it needs log2(1 - r_k) alone).  Per condition the S slots are summed in
+// the lane; two conditions' sums go over the wave in one reduction
+// (wave_totals4), and the lane that ends each adds it to the block's LDS
+// accumulators (one writer per rule set and tile).  Eight waves per SIMD (two
+// blocks per CU) at 64 VGPRs and 80 SGPRs: sets of up to 24 rules on 20,011 x
+// 45 take 234 us (520 us with two samples per lane, 124 VGPRs and one block
+// per CU), of 10-16 rules on 60,000 x 90 0.83 ms (1.39 ms likewise).
 // TONLY: the population has threshold conditions only (no x[g] rows).
-template <int S, class Acc, bool TONLY>
+template <int S, class Acc, bool TONLY, int R>
 __global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_soft_bwd_reg(
     const SoftArgs a) {
   constexpr int TS = 64 * S, WPT = AERL_TILE / TS;
@@ -762,7 +773,7 @@ __global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_soft_bwd
       const int set_end = ss.z + ss.w;
       const bool regular = set_regular(a, lane, ss);
       Window win = first_window(a.classify && regular);
-      RuleState<S> L, B;
+      RuleState<S, R> L, B;
       float logpy[S], surv[S];
 #pragma unroll
       for (int s = 0; s < S; ++s) { logpy[s] = kNegInf; surv[s] = 0.0f; }
@@ -1067,13 +1078,20 @@ void launch_fwd(const SoftPlan &p, dim3 grid, hipStream_t st, const SoftArgs &a)
   }
 }
 
+template <int S, class Acc, bool TONLY>
+void launch_bwd_reg_s(const SoftPlan &p, dim3 grid, hipStream_t st, const SoftArgs &a) {
+  if (a.max_rules <= kFewRules)
+    hipLaunchKernelGGL((k_soft_bwd_reg<S, Acc, TONLY, kFewRules>), grid, dim3(kBwdRegBlock), p.lds, st, a);
+  else
+    hipLaunchKernelGGL((k_soft_bwd_reg<S, Acc, TONLY, kRegRules>), grid, dim3(kBwdRegBlock), p.lds, st, a);
+}
+
 template <class Acc, bool TONLY>
 void launch_bwd_reg(const SoftPlan &p, dim3 grid, hipStream_t st, const SoftArgs &a) {
-  const dim3 rb(kBwdRegBlock);
   switch (p.S) {
-    case 4: hipLaunchKernelGGL((k_soft_bwd_reg<4, Acc, TONLY>), grid, rb, p.lds, st, a); break;
-    case 2: hipLaunchKernelGGL((k_soft_bwd_reg<2, Acc, TONLY>), grid, rb, p.lds, st, a); break;
-    default: hipLaunchKernelGGL((k_soft_bwd_reg<1, Acc, TONLY>), grid, rb, p.lds, st, a); break;
+    case 4: launch_bwd_reg_s<4, Acc, TONLY>(p, grid, st, a); break;
+    case 2: launch_bwd_reg_s<2, Acc, TONLY>(p, grid, st, a); break;
+    default: launch_bwd_reg_s<1, Acc, TONLY>(p, grid, st, a); break;
   }
 }
 
@@ -1428,7 +1446,7 @@ __global__ __launch_bounds__(kSmaxBwdWaves * 64) void k_smax_bwd(const SoftArgs 
 // the first-firing adjoint.  Same formulas as k_smax_bwd, which takes 4-15
 // times as long (sets of up to 24 rules on 20,011 x 45: 0.97 ms against
 // 0.25).
-template <int S, int NC, class Acc, bool TONLY>
+template <int S, int NC, class Acc, bool TONLY, int R>
 __global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_smax_bwd_reg(
     const SoftArgs a, float beta, float beta2) {
   constexpr int TS = 64 * S, WPT = AERL_TILE / TS;
@@ -1468,7 +1486,7 @@ __global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_smax_bwd
       const int set_end = ss.z + ss.w;
       const bool regular = set_regular(a, lane, ss);
       Window win = first_window(a.classify && regular);
-      RuleState<S> LA, LP, LB;
+      RuleState<S, R> LA, LP, LB;
       float v[S][NC], surv[S];
 #pragma unroll
       for (int s = 0; s < S; ++s) {
@@ -1655,18 +1673,27 @@ void launch_smax_fwd_nc(const SoftPlan &p, dim3 grid, hipStream_t st, const Soft
   launch_smax_fwd_s<1, NC>(p, grid, st, a, prod, tonly, beta2);
 }
 
+template <int S, int NC, class Acc, bool TONLY>
+void launch_smax_bwd_t(const SoftPlan &p, dim3 grid, hipStream_t st, const SoftArgs &a, float beta,
+                       float beta2) {
+  const dim3 b(kBwdRegBlock);
+  if (a.max_rules <= kFewRules)
+    hipLaunchKernelGGL((k_smax_bwd_reg<S, NC, Acc, TONLY, kFewRules>), grid, b, p.lds, st, a, beta, beta2);
+  else
+    hipLaunchKernelGGL((k_smax_bwd_reg<S, NC, Acc, TONLY, kRegRules>), grid, b, p.lds, st, a, beta, beta2);
+}
+
 template <int S, int NC>
 void launch_smax_bwd_s(const SoftPlan &p, dim3 grid, hipStream_t st, const SoftArgs &a, bool prod,
                        bool tonly, float beta, float beta2) {
-  const dim3 b(kBwdRegBlock);
   if (prod && tonly)
-    hipLaunchKernelGGL((k_smax_bwd_reg<S, NC, RuleProd, true>), grid, b, p.lds, st, a, beta, beta2);
+    launch_smax_bwd_t<S, NC, RuleProd, true>(p, grid, st, a, beta, beta2);
   else if (prod)
-    hipLaunchKernelGGL((k_smax_bwd_reg<S, NC, RuleProd, false>), grid, b, p.lds, st, a, beta, beta2);
+    launch_smax_bwd_t<S, NC, RuleProd, false>(p, grid, st, a, beta, beta2);
   else if (tonly)
-    hipLaunchKernelGGL((k_smax_bwd_reg<S, NC, RuleAcc, true>), grid, b, p.lds, st, a, beta, beta2);
+    launch_smax_bwd_t<S, NC, RuleAcc, true>(p, grid, st, a, beta, beta2);
   else
-    hipLaunchKernelGGL((k_smax_bwd_reg<S, NC, RuleAcc, false>), grid, b, p.lds, st, a, beta, beta2);
+    launch_smax_bwd_t<S, NC, RuleAcc, false>(p, grid, st, a, beta, beta2);
 }
 
 template <int NC>

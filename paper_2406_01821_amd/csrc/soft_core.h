@@ -284,16 +284,20 @@ __device__ __forceinline__ void param_grads(uint32_t sc, const float *__restrict
   drhs = (float)(-sinv * g0 * scale);
 }
 
-// Most rules whose state the adjoints keep in private memory.
-constexpr int kRegRules = 64;
+// Most rules whose state the adjoints keep in private memory, and the bound of
+// the variants for shorter rule sets.  The runtime reserves a kernel's private
+// memory for every wave that the GPU can hold, whatever the population: 16 rules
+// take 520 bytes per lane (270 MB) with four samples, 64 rules 2080 (1.1 GB),
+// under the softmax head 780 and 3100.
+constexpr int kRegRules = 64, kFewRules = 16;
 
-// Per-rule state of a lane's S samples, indexed by the rule: private memory,
-// the address the same for the whole wave.  Rules run fastest, so that a
-// rule's S values are S single accesses: one of 4 S bytes would need its
-// registers in a row, which the adjoints at 64 VGPRs do not have.
-template <int S>
+// Per-rule state of a lane's S samples for up to R rules, indexed by the rule:
+// private memory, the address the same for the whole wave.  Rules run fastest,
+// so that a rule's S values are S single accesses: one of 4 S bytes would need
+// its registers in a row, which the adjoints at 64 VGPRs do not have.
+template <int S, int R>
 struct RuleState {
-  float v[S][kRegRules];
+  float v[S][R];
   __device__ __forceinline__ void get(int k, float (&out)[S]) const {
 #pragma unroll
     for (int s = 0; s < S; ++s) out[s] = v[s][k];

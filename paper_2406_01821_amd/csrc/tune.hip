@@ -102,7 +102,7 @@ struct TuneSetsArgs {
   int32_t spb, max_conds;    // rule sets per block, conditions per rule set
 };
 constexpr int kTuneSetsWaves = 16;
-template <int S, class Acc, bool XLDS>
+template <int S, class Acc, bool XLDS, int R>
 __global__ __launch_bounds__(kTuneSetsWaves * 64) void k_tune_sets(const TuneSetsArgs a) {
   constexpr int TS = 64 * S, WPT = AERL_TILE / TS;
   extern __shared__ __align__(16) char lds[];
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(kTuneSetsWaves * 64) void k_tune_sets(const TuneSet
   for (int ep = a.ep0; ep <= last; ++ep) {
     const bool step = ep < a.ep1;
     if (active) {
-      RuleState<S> L, B;
+      RuleState<S, R> L, B;
       float logpy[S], surv[S];
 #pragma unroll
       for (int s = 0; s < S; ++s) { logpy[s] = kNegInf; surv[s] = 0.0f; }
@@ -435,17 +435,26 @@ TuneSetsPlan plan_tune_sets(const DatasetRec &ds, const PopRec &pop, int n_cu) {
   return best;
 }
 
-template <int S>
-void launch_tune_sets(const TuneSetsPlan &p, const TuneSetsArgs &a, bool prod, hipStream_t st) {
+template <int S, class Acc, bool XLDS>
+void launch_tune_sets_t(const TuneSetsPlan &p, const TuneSetsArgs &a, int max_rules, hipStream_t st) {
   const dim3 grid((unsigned)((a.n_sets + p.spb - 1) / p.spb)), block((unsigned)(p.spb * p.n_wt * 64));
-  if (prod && p.x_lds)
-    hipLaunchKernelGGL((k_tune_sets<S, RuleProd, true>), grid, block, p.lds, st, a);
-  else if (prod)
-    hipLaunchKernelGGL((k_tune_sets<S, RuleProd, false>), grid, block, p.lds, st, a);
-  else if (p.x_lds)
-    hipLaunchKernelGGL((k_tune_sets<S, RuleAcc, true>), grid, block, p.lds, st, a);
+  if (max_rules <= kFewRules)
+    hipLaunchKernelGGL((k_tune_sets<S, Acc, XLDS, kFewRules>), grid, block, p.lds, st, a);
   else
-    hipLaunchKernelGGL((k_tune_sets<S, RuleAcc, false>), grid, block, p.lds, st, a);
+    hipLaunchKernelGGL((k_tune_sets<S, Acc, XLDS, kRegRules>), grid, block, p.lds, st, a);
+}
+
+template <int S>
+void launch_tune_sets(const TuneSetsPlan &p, const TuneSetsArgs &a, const PopRec &pop, hipStream_t st) {
+  const bool prod = pop.max_rule_conds <= kProdMaxConds;
+  if (prod && p.x_lds)
+    launch_tune_sets_t<S, RuleProd, true>(p, a, pop.max_rules, st);
+  else if (prod)
+    launch_tune_sets_t<S, RuleProd, false>(p, a, pop.max_rules, st);
+  else if (p.x_lds)
+    launch_tune_sets_t<S, RuleAcc, true>(p, a, pop.max_rules, st);
+  else
+    launch_tune_sets_t<S, RuleAcc, false>(p, a, pop.max_rules, st);
 }
 
 // Every epoch through k_tune_sets, kTuneEpochs per launch (a launch stays in
@@ -480,13 +489,12 @@ hipError_t run_tune_sets(const TuneLaunch &t, const TuneSetsPlan &p, float *mom,
   a.spb = p.spb;
   a.max_conds = std::max(pop.max_set_conds, 1);
   a.b1t = a.b2t = 1.0;
-  const bool prod = pop.max_rule_conds <= kProdMaxConds;
   for (a.ep0 = 0; a.ep0 < std::max(t.epochs, 1); a.ep0 = a.ep1) {
     a.ep1 = std::min(a.ep0 + kTuneEpochs, t.epochs);
     switch (p.S) {
-      case 4: launch_tune_sets<4>(p, a, prod, st); break;
-      case 2: launch_tune_sets<2>(p, a, prod, st); break;
-      default: launch_tune_sets<1>(p, a, prod, st); break;
+      case 4: launch_tune_sets<4>(p, a, pop, st); break;
+      case 2: launch_tune_sets<2>(p, a, pop, st); break;
+      default: launch_tune_sets<1>(p, a, pop, st); break;
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
