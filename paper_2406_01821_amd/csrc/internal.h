@@ -61,7 +61,8 @@ aerl_status fail(aerl_ctx *ctx, aerl_status code, const char *fmt, ...);
 // last record of the set's default class, so every walk ends in a commit.
 // Soft condition (caller order): f | g << 12 | feature << 24 | (op >= 2) << 25
 // | categorical << 26; a categorical condition's code set is in the packed
-// image's mask array (caller order, two words per condition).
+// image's mask array (caller order, two words per condition).  Bit 31 is free
+// for the gathered records' mark.
 constexpr uint32_t kSoftFF = 1u << 24, kSoftCat = 1u << 26;
 constexpr uint32_t kRecGMask = 0x1ffu;
 constexpr uint32_t kRecMul = 1u << 0;     // threshold records only

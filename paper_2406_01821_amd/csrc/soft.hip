@@ -314,31 +314,13 @@ struct Window {
 __device__ __forceinline__ Window first_window(bool on) { return {0, on ? 0 : INT32_MAX, 0, 0}; }
 
 // Whether every parameter of a rule set's conditions (ss, its soft record) is
-// one that z2 is not NaN for, on any sample and on the zeros of the padding:
-// not NaN, and but for a threshold not infinite.  Parameters arrive unchecked
-// (an optimizer run that diverges), and what NaN reaches has to show: a set
-// that fails this is swept in full, nothing of it left out as zero.
-// Four records per lane are requested at a time: a set of 1000 conditions
-// waits four times, not sixteen.
-__device__ __forceinline__ bool set_regular(const SoftArgs &a, int lane, int4 ss) {
-  bool odd = false;
-  const uint4 *recs = a.crec + ss.z;
-  const auto look = [&](uint4 r) {
-    const float c = __uint_as_float(r.y), rv = __uint_as_float(r.z), sinv = __uint_as_float(r.w);
-    const bool ok = __builtin_isfinite(c) && __builtin_isfinite(sinv) &&
-                    ((r.x & kSoftFF) ? __builtin_isfinite(rv) : rv == rv);
-    odd = odd || !(ok || (r.x & kSoftCat));
-  };
-  int i = lane;
-  for (; i + 192 < ss.w; i += 256) {
-    uint4 r[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) r[k] = recs[i + 64 * k];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) look(r[k]);
-  }
-  for (; i < ss.w; i += 64) look(recs[i]);
-  return ballot(odd) == 0;
+// one that z2 is not NaN for (record_odd).  Parameters arrive unchecked (an
+// optimizer run that diverges), and what NaN reaches has to show: a set that
+// fails this is swept in full, nothing of it left out as zero.  One scalar
+// load of the mark on the set's first record; looking over the records here
+// instead made the adjoints 1% longer on average and up to 18%.
+__device__ __forceinline__ bool set_regular(const SoftArgs &a, int4 ss) {
+  return !(ldc(a.crec, max(min(ss.z, a.n_conds - 1), 0)).x & kRecOdd);
 }
 template <bool TONLY>
 __device__ __forceinline__ void classify(const SoftArgs &a, const float2 *ext, int lane, int base,
@@ -414,13 +396,22 @@ __device__ __forceinline__ void add_rule(const SoftArgs &a, const float *xs, int
   }
 }
 
-// Gathers the per-condition records read by the kernels above.
-__global__ void k_soft_prep(const uint32_t *__restrict__ sconds, const float *__restrict__ inv_tau,
-                            const float *__restrict__ coef, const float *__restrict__ coef2,
-                            const float *__restrict__ theta, const uint2 *__restrict__ cmask,
-                            int32_t n_conds, uint4 *__restrict__ crec) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < n_conds) crec[j] = cond_record(sconds[j], inv_tau, coef, coef2, theta, cmask, j);
+// Gathers the per-condition records read by the kernels above, a rule set per
+// block, and marks the first one of a set with a record_odd.
+constexpr int kPrepBlock = 256;
+__global__ __launch_bounds__(kPrepBlock) void k_soft_prep(
+    const int4 *__restrict__ ssets, const uint32_t *__restrict__ sconds,
+    const float *__restrict__ inv_tau, const float *__restrict__ coef, const float *__restrict__ coef2,
+    const float *__restrict__ theta, const uint2 *__restrict__ cmask, uint4 *__restrict__ crec) {
+  const int4 ss = ldc(ssets, blockIdx.x);
+  int odd = 0;
+  for (int i = threadIdx.x; i < ss.w; i += blockDim.x) {
+    const int64_t j = (int64_t)ss.z + i;
+    const uint4 r = cond_record(sconds[j], inv_tau, coef, coef2, theta, cmask, j);
+    crec[j] = r;
+    odd |= record_odd(r);
+  }
+  if (__syncthreads_or(odd) && threadIdx.x == 0) crec[ss.z].x |= kRecOdd;
 }
 
 constexpr int kSoftBlock = 512;
@@ -477,7 +468,7 @@ __device__ __forceinline__ void soft_fwd(const SoftArgs a) {
       const int dflt = ldc(a.sets, q0 + q).z;
       const int set_end = ss.z + ss.w;
       Window win;
-      if constexpr (CLS) win = first_window(set_regular(a, lane, ss));
+      if constexpr (CLS) win = first_window(set_regular(a, ss));
       float logpy[S], surv[S];
 #pragma unroll
       for (int s = 0; s < S; ++s) { logpy[s] = kNegInf; surv[s] = 0.0f; }
@@ -771,7 +762,7 @@ __global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_soft_bwd
       const int4 ss = ldc(a.ssets, q0 + q);
       const int dflt = ldc(a.sets, q0 + q).z;
       const int set_end = ss.z + ss.w;
-      const bool regular = set_regular(a, lane, ss);
+      const bool regular = set_regular(a, ss);
       Window win = first_window(a.classify && regular);
       RuleState<S, R> L, B;
       float logpy[S], surv[S];
@@ -1120,10 +1111,10 @@ size_t soft_part_bytes(const DatasetRec &ds, const PopRec &pop, bool backward) {
 }
 
 hipError_t launch_prep(const SoftLaunch &l, const SoftArgs &a, uint4 *crec, hipStream_t st) {
-  const int n = l.pop->n_conds;
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_soft_prep, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a.sconds,
-                     a.inv_tau, a.coef, a.coef2, a.theta, l.pop->cmask, n, crec);
+  if (l.pop->n_conds == 0) return hipSuccess;
+  const dim3 block(l.pop->max_set_conds <= 64 ? 64 : kPrepBlock);
+  hipLaunchKernelGGL(k_soft_prep, dim3((unsigned)l.pop->n_sets), block, 0, st, a.ssets, a.sconds,
+                     a.inv_tau, a.coef, a.coef2, a.theta, l.pop->cmask, crec);
   return hipGetLastError();
 }
 
@@ -1256,7 +1247,7 @@ __device__ __forceinline__ void smax_fwd(const SoftArgs a, float beta2) {
       const int dflt = ldc(a.sets, q0 + q).z;
       const int set_end = ss.z + ss.w;
       Window win;
-      if constexpr (CLS) win = first_window(set_regular(a, lane, ss));
+      if constexpr (CLS) win = first_window(set_regular(a, ss));
       float v[S][NC], surv[S];
 #pragma unroll
       for (int s = 0; s < S; ++s) {
@@ -1484,7 +1475,7 @@ __global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_smax_bwd
       const int4 ss = ldc(a.ssets, q0 + q);
       const int dflt = ldc(a.sets, q0 + q).z;
       const int set_end = ss.z + ss.w;
-      const bool regular = set_regular(a, lane, ss);
+      const bool regular = set_regular(a, ss);
       Window win = first_window(a.classify && regular);
       RuleState<S, R> LA, LP, LB;
       float v[S][NC], surv[S];

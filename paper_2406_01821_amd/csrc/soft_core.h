@@ -250,6 +250,17 @@ __device__ __forceinline__ uint4 cond_record(uint32_t sc, const float *__restric
   return make_uint4(sc, __float_as_uint(coef[j]), __float_as_uint(rv), __float_as_uint(sinv));
 }
 
+// A record whose z2 is NaN for some sample, or on the zeros of the padding: a
+// parameter that is NaN, or but for a threshold infinite.  The first record of
+// a rule set that holds one carries kRecOdd in x.
+constexpr uint32_t kRecOdd = 1u << 31;
+__device__ __forceinline__ bool record_odd(uint4 r) {
+  if (r.x & kSoftCat) return false;
+  const float c = __uint_as_float(r.y), rv = __uint_as_float(r.z), sinv = __uint_as_float(r.w);
+  return !(__builtin_isfinite(c) && __builtin_isfinite(sinv) &&
+           ((r.x & kSoftFF) ? __builtin_isfinite(rv) : rv == rv));
+}
+
 // Sums a condition's partial gradients [n_groups][n_conds][2] in group order,
 // eight loads in flight at a time.
 __device__ __forceinline__ void sum_groups(const float *__restrict__ part, int n_groups,

@@ -72,3 +72,24 @@ def test_nan_shows(ctx, n, nf, rules, far, kind, which):
         assert np.isnan(got[head + 2][own[ff]]).all() and np.isnan(got[head + 3][own[~ff]]).all()
         for a, b in zip(got[head + 1:head + 4], plain[head + 1:head + 4]):
             assert np.array_equal(a[outside], b[outside])
+
+
+@pytest.mark.parametrize("n", [700, 5000])
+def test_a_run_that_diverges_is_one_run(ctx, n):
+    """Gradient descent whose first step takes parameters past the float
+    range: the records that the update writes for the next epoch mark such a
+    rule set as the ones gathered anew after a loss pass do, so a run with a
+    loss history and one without end in the same bits."""
+    import torch
+    w = synth.tiny(n, n=n, nf=9, n_classes=3, n_sets=30, rules=(0, 8), conds=(1, 4), ff_frac=0.3)
+    ds = ctx.upload_dataset(w.data)
+    p = ctx.pack_population(w.pop, 9, 3)
+    out = []
+    for hist in (False, True):
+        v = [torch.tensor(a, device=ctx.device) for a in (w.pop.coef, w.pop.coef2, w.pop.theta)]
+        ctx.finetune(ds, p, *v, 3, optimizer="sgd", lr=3e38, loss_history=hist)
+        torch.cuda.synchronize()
+        out.append([t.cpu().numpy() for t in v])
+    assert not all(np.isfinite(a).all() for a in out[0])
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
