@@ -30,6 +30,7 @@
 #include "eval_core.h"
 #include "internal.h"
 #include "soft_core.h"
+#include "soft_plan.h"
 
 namespace aerl {
 
@@ -414,7 +415,6 @@ __global__ __launch_bounds__(kPrepBlock) void k_soft_prep(
   if (__syncthreads_or(odd) && threadIdx.x == 0) crec[ss.z].x |= kRecOdd;
 }
 
-constexpr int kSoftBlock = 512;
 // Eight waves per SIMD need at most 80 SGPRs per wave (measured on gfx950):
 // the classifying forward sweeps would take 106 and leave seven (forward and
 // adjoint on 262,144 x 32, 1024 rule sets: 11.97 ms, capped 11.70 ms).
@@ -542,10 +542,6 @@ __global__ __launch_bounds__(kFwdFinalWaves * 64) void k_soft_fwd_final(
 }
 
 // ----------------------------------------------------------------- backward
-// Waves per block of the LDS-state adjoint kernels: up to kBwdWaves, fewer
-// for rule sets whose per-wave state ([R][2][64] floats) would not fit.
-constexpr int kBwdWaves = 8;
-
 __global__ __launch_bounds__(kBwdWaves * 64) void k_soft_bwd(const SoftArgs a) {
   constexpr int TS = 64, WPT = AERL_TILE / TS;
   extern __shared__ __align__(16) float smem[];
@@ -702,10 +698,6 @@ __device__ __forceinline__ void bwd_rule_conds(const SoftArgs &a, const float *x
   }
 }
 
-// 16 waves share a block's tile and accumulators in LDS, so the LDS limit
-// still leaves 32 waves per CU.
-constexpr int kBwdRegBlock = 1024;
-
 // Adjoint for rule sets of at most kRegRules rules with S samples per lane:
 // the per-rule state kept between the two sweeps is l_k = a_k + (survival
 // before k) and log2(1 - r_k), in per-lane private memory (scratch, served by
@@ -727,8 +719,8 @@ __global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_soft_bwd
   constexpr int TS = 64 * S, WPT = AERL_TILE / TS;
   extern __shared__ __align__(16) float smem[];
   float *xs = smem;                                             // [nf][TS]
-  float2 *ext = reinterpret_cast<float2 *>(xs + (size_t)a.nf * TS);  // [nf]
-  float *acc = reinterpret_cast<float *>(ext + a.nf);                // [Q][max_set_conds][2]
+  float2 *ext = reinterpret_cast<float2 *>(xs + (size_t)a.nf * TS);  // [nf] when tiles classify
+  float *acc = reinterpret_cast<float *>(ext + (a.classify ? a.nf : 0));  // [Q][max_set_conds][2]
   __shared__ int32_t next_q;
   const int lane = threadIdx.x & 63;
   int label, tile_lo, tile_hi;
@@ -878,149 +870,6 @@ __global__ void k_soft_bwd_final(const float *__restrict__ part, int32_t n_group
   }
 }
 
-struct SoftPlan {
-  int S, Q, TG, n_groups;
-  bool reg;   // backward: per-rule state in private memory, else in LDS
-  bool cls;   // forward: tiles classify the conditions
-  int waves;  // LDS-state kernels: waves per block
-  size_t lds;
-};
-
-// Adjoints of tables of at least this many tiles classify conditions per tile.
-// On fewer, a tile spans most of each column's range and little is decided: the
-// adjoint of 100 rule sets on 569 samples takes 46.0 us with and 45.0 us
-// without it, on 4000 samples 47.5 and 46.8 us (94 and 96 us with longer rule
-// sets).
-constexpr int64_t kClassifyTiles = 16;
-
-// Feature tile and its extremes.
-size_t tile_lds(int nf, int S) { return (size_t)nf * 64 * S * 4 + (size_t)nf * sizeof(float2); }
-
-// Waves and rule-set chunk of an LDS-state adjoint kernel (tile xs bytes,
-// per_set accumulator bytes, per_wave state bytes): the most waves (at most
-// max_waves) that fit with one rule set per chunk, then the largest chunk
-// (at most max_q sets) that fits.
-void lds_state_plan(SoftPlan &p, size_t xs, size_t per_set, size_t per_wave, int max_waves,
-                    int max_q, int n_sets) {
-  p.waves = max_waves;
-  while (p.waves > 1 && xs + per_set + p.waves * per_wave > kDynLdsMax) p.waves >>= 1;
-  p.Q = std::max(1, std::min(n_sets, max_q));
-  while (p.Q > 1 && xs + p.Q * per_set + p.waves * per_wave > kDynLdsMax) p.Q >>= 1;
-  p.lds = xs + (size_t)p.Q * per_set + p.waves * per_wave;
-}
-
-int64_t count_groups(const DatasetRec &ds, int tg) {
-  int64_t g = 0;
-  for (int c = 0; c < ds.nc; ++c) g += (ds.region_tiles[c] + tg - 1) / tg;
-  return g;
-}
-
-// Tiles per block group.  A launch has (set chunks) x (tile groups) blocks;
-// the fewest groups that still give about `target` blocks (measured on the
-// 262,144 x 32, 1024-set workload: a forward grid of one wave of blocks,
-// 64 groups, runs 10.9 ms, 1024 groups 6.9 ms, as its blocks no longer stage
-// their tiles in step; the adjoint runs 22.8 ms at 64 groups and 20.8 ms at
-// 256), then fewer while the per-group partial sums (bytes_per_group each)
-// exceed max_bytes.
-int tiles_per_group(const DatasetRec &ds, int64_t chunks, int64_t target, size_t bytes_per_group,
-                    size_t max_bytes) {
-  int32_t widest = 1;
-  for (int c = 0; c < ds.nc; ++c) widest = std::max(widest, ds.region_tiles[c]);
-  const int64_t need = (target + std::max<int64_t>(chunks, 1) - 1) / std::max<int64_t>(chunks, 1);
-  int tg = 1;
-  while (tg < widest && count_groups(ds, 2 * tg) >= need) tg *= 2;
-  while (tg < widest && (size_t)count_groups(ds, tg) * bytes_per_group > max_bytes) tg *= 2;
-  return tg;
-}
-// Forward: 16 blocks per block slot (four 512-thread blocks per CU on 256
-// CUs), fp64 partials of at most 8 MiB (half the no-allocation scratch).
-constexpr int64_t kFwdTargetBlocks = 16384;
-constexpr size_t kFwdPartMax = (size_t)8 << 20;
-// Backward: 8 blocks per slot (two 1024-thread blocks per CU), partial
-// gradients of at most 1 GiB.
-constexpr int64_t kBwdTargetBlocks = 4096;
-constexpr size_t kBwdPartMax = (size_t)1 << 30;
-
-// Rule sets per block: 64, or fewer, down to one per wave (min_q), while
-// the grid (set chunks x `groups` tile groups) stays under `target` blocks,
-// so that a small workload spreads over more CUs instead of walking several
-// rule sets per wave on a few of them.
-int sets_per_block(int n_sets, int64_t groups, int64_t target, int min_q) {
-  int q = std::max(1, std::min(n_sets, 64));
-  while (q / 2 >= min_q && (int64_t)((n_sets + q - 1) / q) * groups < target) q /= 2;
-  return q;
-}
-
-// Whether a forward pass classifies.  Per tile it costs the extremes (a pass
-// over nf rows) and per rule set and 64 conditions a classification, and it
-// saves a share of the sweep that grows with the conditions of a rule (one out
-// of reach drops the rule).  Of 270 shapes timed both ways the line falls where
-// a launch has 600,000 (tile, condition) pairs (60,000 x 32, 40 rule sets of 8
-// x 4 conditions: 45 us, plain 55; 262,144 x 32 x 1024 of 16 x 4: 3.0 and 6.5
-// ms); on wider tables, whose tiles are half or a quarter as long for the same
-// extremes, only with enough rule sets per block (30,000 x 90 x 200 of 8-16 x
-// 2-5: 190 and 180 us).  Smaller launches gain on narrow tables alone (40,000 x
-// 60, 16 rule sets: 37 and 28 us; 20,011 x 45, 150 of 1-24 x 1-6: 98 and 104),
-// by rules of more than two conditions or many of them per staged value (23,741
-// x 38, 32 of 24 x 2: 52 and 49 us).  Rules of more than 64 conditions are
-// swept in full in any case.
-bool forward_classifies(const DatasetRec &ds, const PopRec &pop, int sets_per_block) {
-  if (ds.n_tiles < kClassifyTiles || pop.n_conds > 72LL * pop.n_rules) return false;
-  const double per_block = (double)sets_per_block * pop.n_conds / std::max(pop.n_sets, 1);
-  if ((double)ds.n_tiles * pop.n_conds >= 6e5) return ds.nf <= 64 || per_block >= 8.0 * ds.nf;
-  return ds.n_tiles >= 24 && ds.nf <= 52 && per_block >= 200 &&
-         (pop.n_conds >= 2.5 * pop.n_rules || per_block >= 12.0 * ds.nf);
-}
-
-// Forward tile and, with cls, its extremes.
-size_t fwd_tile_lds(int nf, int S, bool cls) { return cls ? tile_lds(nf, S) : (size_t)nf * 64 * S * 4; }
-
-SoftPlan plan_forward(const DatasetRec &ds, const PopRec &pop) {
-  SoftPlan p{};
-  p.Q = sets_per_block(pop.n_sets, count_groups(ds, 1), kFwdTargetBlocks, kSoftBlock / 64);
-  p.cls = forward_classifies(ds, pop, p.Q);
-  // four samples per lane; where tiles classify, while three blocks fit a CU
-  // (60,000 x 60, where two would: 611 us, with two samples per lane 560 us)
-  p.S = !p.cls || tile_lds(ds.nf, 4) <= kLdsPerCu / 3 ? 4 : 2;
-  while (p.S > 1 && (size_t)ds.nf * 256 * p.S > 64 * 1024) p.S >>= 1;
-  p.TG = tiles_per_group(ds, (pop.n_sets + p.Q - 1) / p.Q, kFwdTargetBlocks,
-                         (size_t)std::max(pop.n_sets, 1) * sizeof(double), kFwdPartMax);
-  p.n_groups = (int)count_groups(ds, p.TG);
-  p.lds = fwd_tile_lds(ds.nf, p.S, p.cls) + (size_t)p.Q * 8;
-  return p;
-}
-
-// Plan of an LDS-state adjoint kernel (one sample per lane).
-SoftPlan plan_lds_state(const DatasetRec &ds, const PopRec &pop, SoftPlan p, int max_waves) {
-  p.reg = false;
-  p.S = 1;
-  lds_state_plan(p, (size_t)ds.nf * 64 * 4, (size_t)std::max(pop.max_set_conds, 1) * 2 * 4,
-                 (size_t)std::max(pop.max_rules, 1) * 128 * 4, max_waves, 16, pop.n_sets);
-  return p;
-}
-
-// Backward: per-rule state in private memory up to kRegRules rules (max_s or
-// fewer samples per lane, so that a tile takes at most 64 KiB), else in LDS.
-SoftPlan plan_adjoint(const DatasetRec &ds, const PopRec &pop, int max_s, int lds_waves) {
-  SoftPlan p{};
-  const size_t per_set = (size_t)std::max(pop.max_set_conds, 1) * 2 * 4;
-  p.TG = tiles_per_group(ds, (pop.n_sets + 63) / 64, kBwdTargetBlocks,
-                         (size_t)std::max(pop.n_conds, 1) * 2 * sizeof(float), kBwdPartMax);
-  p.n_groups = (int)count_groups(ds, p.TG);
-  if (pop.max_rules > kRegRules) return plan_lds_state(ds, pop, p, lds_waves);
-  p.reg = true;
-  p.S = max_s;
-  while (p.S > 1 && (size_t)ds.nf * 256 * p.S > 64 * 1024) p.S >>= 1;
-  const size_t xs = tile_lds(ds.nf, p.S);
-  p.Q = sets_per_block(pop.n_sets, p.n_groups, kBwdTargetBlocks, kBwdRegBlock / 64);
-  while (p.Q > 1 && xs + p.Q * per_set > kLdsPerCu / 2 - kStaticLds) p.Q >>= 1;  // two blocks per CU
-  p.lds = xs + (size_t)p.Q * per_set;
-  return p;
-}
-SoftPlan plan_backward(const DatasetRec &ds, const PopRec &pop) {
-  return plan_adjoint(ds, pop, 4, kBwdWaves);
-}
-
 void fill_args(SoftArgs &a, const SoftLaunch &l, const SoftPlan &p) {
   const DatasetRec &ds = *l.ds;
   const PopRec &pop = *l.pop;
@@ -1043,7 +892,7 @@ void fill_args(SoftArgs &a, const SoftLaunch &l, const SoftPlan &p) {
   a.sets_per_chunk = p.Q;
   a.tiles_per_group = p.TG;
   a.n_groups = p.n_groups;
-  a.classify = ds.n_tiles >= kClassifyTiles;
+  a.classify = p.cls;
   a.max_rules = std::max(pop.max_rules, 1);
   a.max_set_conds = std::max(pop.max_set_conds, 1);
   for (int c = 0; c < ds.nc; ++c) {
@@ -1206,8 +1055,6 @@ __device__ __forceinline__ float smax_log2py(const float (&v)[NC], int nc, float
   }
   return ty - m - flog2(sum);
 }
-
-constexpr int kSmaxBwdWaves = 4;
 
 template <int S, int NC, class Acc, bool TONLY, bool CLS>
 __device__ __forceinline__ void smax_fwd(const SoftArgs a, float beta2) {
@@ -1443,8 +1290,8 @@ __global__ __launch_bounds__(kBwdRegBlock, 8) AERL_SOFT_SGPR_CAP void k_smax_bwd
   constexpr int TS = 64 * S, WPT = AERL_TILE / TS;
   extern __shared__ __align__(16) float smem[];
   float *xs = smem;                                             // [nf][TS]
-  float2 *ext = reinterpret_cast<float2 *>(xs + (size_t)a.nf * TS);  // [nf]
-  float *acc = reinterpret_cast<float *>(ext + a.nf);                // [Q][max_set_conds][2]
+  float2 *ext = reinterpret_cast<float2 *>(xs + (size_t)a.nf * TS);  // [nf] when tiles classify
+  float *acc = reinterpret_cast<float *>(ext + (a.classify ? a.nf : 0));  // [Q][max_set_conds][2]
   __shared__ int32_t next_q;
   const int lane = threadIdx.x & 63;
   int label, tile_lo, tile_hi;
@@ -1609,27 +1456,6 @@ __global__ __launch_bounds__(256) void k_smax_proba(const float *__restrict__ ro
   float p[NC];
   (void)smax_log2py(v, nc, beta2, 0, p);
   for (int c = 0; c < nc; ++c) probs[i * nc + c] = p[c];
-}
-
-int smax_nc(int nc) { return nc <= 2 ? 2 : nc <= 4 ? 4 : nc <= 8 ? 8 : 16; }
-
-SoftPlan plan_smax_backward(const DatasetRec &ds, const PopRec &pop) {
-  return plan_adjoint(ds, pop, std::min(4, 16 / smax_nc(ds.nc)), kSmaxBwdWaves);
-}
-
-// Same groups (and so the same workspace) as the first-firing forward.  Four
-// samples per lane up to four classes and while three blocks fit a CU
-// (20,011 x 45, 150 mixed rule sets: 94 us, with two samples 111 us; 60,000 x
-// 60, where two would fit: 576 and 517 us), but not in a plain sweep of rules
-// past the product form, whose registers would leave four waves per SIMD; else
-// two, one where two do not fit.
-SoftPlan plan_smax_forward(const DatasetRec &ds, const PopRec &pop) {
-  SoftPlan p = plan_forward(ds, pop);
-  const bool wide = p.cls || pop.max_rule_conds <= kProdMaxConds;
-  p.S = smax_nc(ds.nc) <= 4 && wide && fwd_tile_lds(ds.nf, 4, p.cls) <= kLdsPerCu / 3 ? 4 : 2;
-  if (fwd_tile_lds(ds.nf, p.S, p.cls) + (size_t)p.Q * 8 > kDynLdsMax) p.S = 1;
-  p.lds = fwd_tile_lds(ds.nf, p.S, p.cls) + (size_t)p.Q * 8;
-  return p;
 }
 
 template <int S, int NC, class Acc, bool TONLY>

@@ -4,6 +4,7 @@
 
 #include "eval_core.h"
 #include "internal.h"
+#include "soft_plan.h"
 
 namespace aerl {
 
@@ -117,7 +118,6 @@ __device__ __forceinline__ float log2_1p(float p) {
 // once per rule.  p is
 // kept scaled by 2^64 (pt), so that u down to 2^-190 stays a normal float;
 // with at most 60 conditions pt < 2^124.
-constexpr int kProdMaxConds = 60;
 // min(v, 0) in one v_min_f32.  fminf on a value the compiler cannot prove
 // canonical (here a product carried across the wave reductions' branches)
 // gets a canonicalizing copy first; no signaling NaN reaches this point, so
@@ -294,13 +294,6 @@ __device__ __forceinline__ void param_grads(uint32_t sc, const float *__restrict
   dcoef = (float)(sinv * g1 * scale);
   drhs = (float)(-sinv * g0 * scale);
 }
-
-// Most rules whose state the adjoints keep in private memory, and the bound of
-// the variants for shorter rule sets.  The runtime reserves a kernel's private
-// memory for every wave that the GPU can hold, whatever the population: 16 rules
-// take 520 bytes per lane (270 MB) with four samples, 64 rules 2080 (1.1 GB),
-// under the softmax head 780 and 3100.
-constexpr int kRegRules = 64, kFewRules = 16;
 
 // Per-rule state of a lane's S samples for up to R rules, indexed by the rule:
 // private memory, the address the same for the whole wave.  Rules run fastest,

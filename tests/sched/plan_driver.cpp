@@ -1,0 +1,37 @@
+// Prints the launch plans of the relaxed path for shapes read from stdin, one
+// per line: features, classes, samples, rule sets, rules per set, conditions
+// per rule.  Output: S Q blocks-per-CU groups LDS of the first-firing adjoint.
+#include <cstdio>
+
+#include "soft_plan.h"
+
+int main() {
+  using namespace aerl;
+  long long n;
+  int nf, nc, sets, rules, conds;
+  while (std::scanf("%d %d %lld %d %d %d", &nf, &nc, &n, &sets, &rules, &conds) == 6) {
+    DatasetRec ds;
+    ds.nf = nf;
+    ds.nc = nc;
+    ds.n = n;
+    for (int c = 0; c < nc; ++c) {
+      ds.class_count[c] = n / nc + (c < n % nc);
+      ds.region_tile0[c] = (int32_t)ds.n_tiles;
+      ds.region_tiles[c] = (int32_t)((ds.class_count[c] + AERL_TILE - 1) / AERL_TILE);
+      ds.n_tiles += ds.region_tiles[c];
+    }
+    ds.n_pad = ds.n_tiles * AERL_TILE;
+    PopRec pop;
+    pop.nf = nf;
+    pop.nc = nc;
+    pop.n_sets = sets;
+    pop.n_rules = sets * rules;
+    pop.n_conds = pop.n_rules * conds;
+    pop.max_rules = rules;
+    pop.max_rule_conds = conds;
+    pop.max_set_conds = rules * conds;
+    const SoftPlan p = plan_backward(ds, pop);
+    std::printf("%d %d %d %d %zu %d\n", p.S, p.Q, 2 * (p.lds + kStaticLds) <= kLdsPerCu ? 2 : 1, p.n_groups,
+                p.lds, (int)p.cls);
+  }
+}

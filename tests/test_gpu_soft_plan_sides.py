@@ -1,14 +1,15 @@
-"""Forward passes of both relaxed heads on either side of the rule that decides
-whether tiles classify the conditions: the fp64 oracle, and a rule set's loss
-is the same whether its population is small enough for the plain sweep or
-large enough to classify (one rounding of the result: the samples' terms are
-the same bits, the tiles' sums are added in fp64 in another grouping)."""
+"""The relaxed path on either side of the rules that decide whether tiles
+classify the conditions and how many rule sets a block takes: the fp64 oracle,
+and a rule set's loss is the same whether its population is small enough for
+the plain sweep or large enough to classify (one rounding of the result: the
+samples' terms are the same bits, the tiles' sums are added in fp64 in another
+grouping)."""
 import numpy as np
 import pytest
 
 import oracle
 from paper_2406_01821_amd import synth
-from test_gpu_soft import check_loss
+from test_gpu_soft import check_grad, check_loss
 
 pytestmark = pytest.mark.gpu
 
@@ -23,15 +24,17 @@ def ctx():
     c.close()
 
 
-def losses(ctx, data, pop):
+def results(ctx, data, pop):
     import torch
     ds = ctx.upload_dataset(data)
     p = ctx.pack_population(pop, data.n_features, data.n_classes)
     v = [torch.tensor(a, device=ctx.device) for a in (pop.coef, pop.coef2, pop.theta)]
     out = [ctx.soft_forward(ds, p, *v).cpu().numpy(), ctx.softmax_forward(ds, p, *v, 2.0).cpu().numpy()]
+    one = torch.ones(pop.n_sets, device=ctx.device)
+    grads = [g.cpu().numpy() for g in ctx.soft_backward(ds, p, *v, one)]
     ctx.release_population(p)
     ctx.release_dataset(ds)
-    return out
+    return out, grads
 
 
 # n, features, classes, rule sets of the large population, rules, conditions:
@@ -46,8 +49,13 @@ def losses(ctx, data, pop):
 def test_plain_and_classifying_sweeps_agree(ctx, n, nf, nc, many, rules, conds, ff):
     w = synth.tiny(n + nf, n=n, nf=nf, n_classes=nc, n_sets=many, rules=rules, conds=conds, ff_frac=ff)
     few = w.pop.subset(range(6))
-    small, large = losses(ctx, w.data, few), losses(ctx, w.data, w.pop)
-    ref = oracle.soft_forward(w.data.x, w.data.y, oracle.tau(w.data.x), nc, few)
-    check_loss(small[0], ref)
+    (small, gs), (large, gl) = results(ctx, w.data, few), results(ctx, w.data, w.pop)
+    x, y, tau = w.data.x, w.data.y, oracle.tau(w.data.x)
+    check_loss(small[0], oracle.soft_forward(x, y, tau, nc, few))
     for a, b in zip(small, large):
         np.testing.assert_allclose(a, b[:6], rtol=1.2e-7, atol=0)
+    if conds[1] > 8:  # rules that long have gradients below the fp32 range here
+        return
+    ref = oracle.soft_backward(x, y, tau, nc, few, dloss=np.ones(6))
+    check_grad(gs, ref)
+    check_grad([g[:few.n_conds] for g in gl], ref)
