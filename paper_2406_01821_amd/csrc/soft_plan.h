@@ -245,6 +245,13 @@ SoftPlan plan_smax_forward(const DatasetRec &ds, const PopRec &pop) {
   return p;
 }
 
+// Where an update's parameter k (0 the coefficient, 1 the right-hand operand)
+// of condition j has its moment: [2][n_conds], past 2^31 entries from 2^30
+// conditions on.
+__host__ __device__ inline int64_t moment_index(int k, int32_t n_conds, int32_t j) {
+  return (int64_t)k * n_conds + j;
+}
+
 }  // namespace
 
 }  // namespace aerl

@@ -57,8 +57,9 @@ __global__ __launch_bounds__(64) void k_tune_update(
   float *rhs = (sc & kSoftFF) ? coef2 : theta;
   float c = coef[j], r = rhs[j];
   if (o.kind == AERL_OPT_ADAM) {
+    const int64_t k = moment_index(1, n_conds, j);
     c = adam(o, c, dc, m[j], v[j], c1, c2);
-    r = adam(o, r, dr, m[n_conds + j], v[n_conds + j], c1, c2);
+    r = adam(o, r, dr, m[k], v[k], c1, c2);
   } else {
     c -= o.lr * dc;
     r -= o.lr * dr;

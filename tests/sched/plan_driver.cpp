@@ -7,6 +7,11 @@
 
 int main() {
   using namespace aerl;
+  // the moments of a population past 2^30 conditions
+  static_assert(sizeof(moment_index(1, 0, 0)) == 8, "64-bit index");
+  if (moment_index(1, 1 << 30, (1 << 30) - 1) != (1LL << 31) - 1 ||
+      moment_index(1, 0x7fffffff, 0x7ffffffe) != 2LL * 0x7fffffff - 1)
+    return 1;
   long long n;
   int nf, nc, sets, rules, conds;
   while (std::scanf("%d %d %lld %d %d %d", &nf, &nc, &n, &sets, &rules, &conds) == 6) {

@@ -25,6 +25,7 @@ def plans(tmp_path_factory):
     def run(shapes):
         r = subprocess.run([exe], input="\n".join(" ".join(map(str, s)) for s in shapes),
                            capture_output=True, text=True, timeout=60)
+        assert r.returncode == 0  # the driver's own check of the moments' index
         return [tuple(map(int, line.split())) for line in r.stdout.splitlines()]
     return run
 
