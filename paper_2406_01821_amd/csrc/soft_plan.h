@@ -245,6 +245,59 @@ SoftPlan plan_smax_forward(const DatasetRec &ds, const PopRec &pop) {
   return p;
 }
 
+// k_tune_sets takes tables of up to kTuneSetsTiles tiles, each wave tile with
+// a wave of its own in a block, and populations whose blocks are resident at
+// once, by LDS and by waves, with the fewest samples per lane that leave a
+// block per CU (latency: 569 samples, 100 rule sets, 50 epochs: one 0.71, two
+// 0.84, four 1.20 ms).  On more tiles a rule set outgrows one CU: 1500 samples
+// 1.15 against 2.47 ms, but 4000 samples 2.40 against 2.18, 3000 x 60 with 400
+// rule sets 5.2 against 4.1 ms.  Blocks past those resident start where the
+// first ones end: up to half as many more still pay where rule sets differ in
+// length, so that some end early (2048 x 30, 10 epochs: 520 rule sets of 1-8 x
+// 1-4 conditions 0.51 ms against the adjoint kernel's 0.68, 1000 of them 0.79
+// against 0.71; 2000 x 8, 700 rule sets of 8 x 4 0.91 against 0.87).
+constexpr int64_t kTuneSetsTiles = 8;
+constexpr int kTuneSetsWaves = 16;
+struct TuneSetsPlan {
+  bool use, x_lds;
+  int S, n_wt, spb;
+  size_t lds;
+};
+// Waves of k_tune_sets that one SIMD holds, by its registers (S = 4: up to 87
+// VGPRs; all: 106 SGPRs).
+int tune_sets_waves_per_simd(int S) { return S == 4 ? 5 : 7; }
+
+TuneSetsPlan plan_tune_sets(const DatasetRec &ds, const PopRec &pop, int n_cu) {
+  TuneSetsPlan best{};
+  const bool uneven = 2LL * pop.max_set_conds * pop.n_sets >= 3LL * pop.n_conds;
+  if (pop.max_rules > kRegRules || ds.n_tiles < 1 || ds.n_tiles > kTuneSetsTiles || pop.n_conds < 1)
+    return best;
+  for (int S = 4; S >= 1; S >>= 1) {
+    if (S > 1 && (size_t)ds.nf * 256 * S > 64 * 1024) continue;  // the adjoint's bound
+    TuneSetsPlan p{};
+    const int64_t n_wt = ds.n_tiles * (AERL_TILE / (64 * S));
+    if (n_wt > kTuneSetsWaves) break;
+    p.S = S;
+    p.n_wt = (int)n_wt;
+    // rule sets per block: one, or more until there is a block per CU
+    p.spb = 1;
+    while ((p.spb + 1) * p.n_wt <= kTuneSetsWaves && (pop.n_sets + p.spb - 1) / p.spb > n_cu) ++p.spb;
+    const size_t waves = (size_t)p.spb * p.n_wt;
+    const size_t own = (waves + 1) / 2 * 2 * sizeof(double) +
+                       (size_t)std::max(pop.max_set_conds, 1) * (p.spb * 32 + waves * 2 * sizeof(float));
+    const size_t table = (size_t)ds.nf * (size_t)ds.n_pad * sizeof(float);
+    p.x_lds = table + own <= kDynLdsMax;
+    p.lds = own + (p.x_lds ? table : 0);
+    const int64_t blocks = (pop.n_sets + p.spb - 1) / p.spb;
+    const int64_t by_lds = (int64_t)(kLdsPerCu / (p.lds + kStaticLds));
+    const int64_t by_waves = tune_sets_waves_per_simd(S) / (int64_t)((waves + 3) / 4);
+    const int64_t resident = std::min<int64_t>({by_lds, by_waves, 2}) * n_cu;
+    p.use = blocks <= resident || (uneven && 2 * blocks <= 3 * resident);
+    if (p.use && (!best.use || blocks <= n_cu)) best = p;
+  }
+  return best;
+}
+
 // Where an update's parameter k (0 the coefficient, 1 the right-hand operand)
 // of condition j has its moment: [2][n_conds], past 2^31 entries from 2^30
 // conditions on.

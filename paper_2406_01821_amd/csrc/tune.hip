@@ -123,7 +123,6 @@ struct TuneSetsArgs {
   Opt opt;
   int32_t spb, max_conds;    // rule sets per block, conditions per rule set
 };
-constexpr int kTuneSetsWaves = 16;
 template <int S, class Acc, bool XLDS, int R>
 __global__ __launch_bounds__(kTuneSetsWaves * 64) void k_tune_sets(const TuneSetsArgs a) {
   constexpr int TS = 64 * S, WPT = AERL_TILE / TS;
@@ -415,47 +414,6 @@ TuneLayout tune_layout(const DatasetRec &ds, const PopRec &pop) {
 }
 
 namespace {
-
-// k_tune_sets takes tables of up to kTuneSetsTiles tiles, each wave tile with
-// a wave of its own in a block, and populations whose blocks are resident at
-// once, with the fewest samples per lane that leave a block per CU (latency:
-// 569 samples, 100 rule sets, 50 epochs: one 0.71, two 0.84, four 1.20 ms).
-// On more tiles a rule set outgrows one CU: 1500 samples 1.15 against 2.47
-// ms, but 4000 samples 2.40 against 2.18, 3000 x 60 with 400 rule sets 5.2
-// against 4.1 ms.
-constexpr int64_t kTuneSetsTiles = 8;
-struct TuneSetsPlan {
-  bool use, x_lds;
-  int S, n_wt, spb;
-  size_t lds;
-};
-TuneSetsPlan plan_tune_sets(const DatasetRec &ds, const PopRec &pop, int n_cu) {
-  TuneSetsPlan best{};
-  if (pop.max_rules > kRegRules || ds.n_tiles < 1 || ds.n_tiles > kTuneSetsTiles || pop.n_conds < 1)
-    return best;
-  for (int S = 4; S >= 1; S >>= 1) {
-    if (S > 1 && (size_t)ds.nf * 256 * S > 64 * 1024) continue;  // the adjoint's bound
-    TuneSetsPlan p{};
-    const int64_t n_wt = ds.n_tiles * (AERL_TILE / (64 * S));
-    if (n_wt > kTuneSetsWaves) break;
-    p.S = S;
-    p.n_wt = (int)n_wt;
-    // rule sets per block: one, or more until there is a block per CU
-    p.spb = 1;
-    while ((p.spb + 1) * p.n_wt <= kTuneSetsWaves && (pop.n_sets + p.spb - 1) / p.spb > n_cu) ++p.spb;
-    const size_t waves = (size_t)p.spb * p.n_wt;
-    const size_t own = (waves + 1) / 2 * 2 * sizeof(double) +
-                       (size_t)std::max(pop.max_set_conds, 1) * (p.spb * 32 + waves * sizeof(float2));
-    const size_t table = (size_t)ds.nf * (size_t)ds.n_pad * sizeof(float);
-    p.x_lds = table + own <= kDynLdsMax;
-    p.lds = own + (p.x_lds ? table : 0);
-    const int64_t blocks = (pop.n_sets + p.spb - 1) / p.spb;
-    const int per_cu = (int)std::min<size_t>(kLdsPerCu / (p.lds + kStaticLds), 2);
-    p.use = blocks <= (int64_t)per_cu * n_cu;
-    if (p.use && (!best.use || blocks <= n_cu)) best = p;
-  }
-  return best;
-}
 
 template <int S, class Acc, bool XLDS>
 void launch_tune_sets_t(const TuneSetsPlan &p, const TuneSetsArgs &a, int max_rules, hipStream_t st) {

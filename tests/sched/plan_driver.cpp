@@ -1,6 +1,8 @@
 // Prints the launch plans of the relaxed path for shapes read from stdin, one
 // per line: features, classes, samples, rule sets, rules per set, conditions
-// per rule.  Output: S Q blocks-per-CU groups LDS of the first-firing adjoint.
+// per rule, conditions of the longest set.  Output: S Q blocks-per-CU groups LDS
+// and classification of the first-firing adjoint, then of the fine-tuning kernel
+// on 256 CUs whether it is used, S, blocks, waves per block and LDS.
 #include <cstdio>
 
 #include "soft_plan.h"
@@ -13,8 +15,8 @@ int main() {
       moment_index(1, 0x7fffffff, 0x7ffffffe) != 2LL * 0x7fffffff - 1)
     return 1;
   long long n;
-  int nf, nc, sets, rules, conds;
-  while (std::scanf("%d %d %lld %d %d %d", &nf, &nc, &n, &sets, &rules, &conds) == 6) {
+  int nf, nc, sets, rules, conds, longest;
+  while (std::scanf("%d %d %lld %d %d %d %d", &nf, &nc, &n, &sets, &rules, &conds, &longest) == 7) {
     DatasetRec ds;
     ds.nf = nf;
     ds.nc = nc;
@@ -34,9 +36,11 @@ int main() {
     pop.n_conds = pop.n_rules * conds;
     pop.max_rules = rules;
     pop.max_rule_conds = conds;
-    pop.max_set_conds = rules * conds;
+    pop.max_set_conds = longest;
     const SoftPlan p = plan_backward(ds, pop);
-    std::printf("%d %d %d %d %zu %d\n", p.S, p.Q, 2 * (p.lds + kStaticLds) <= kLdsPerCu ? 2 : 1, p.n_groups,
-                p.lds, (int)p.cls);
+    const TuneSetsPlan t = plan_tune_sets(ds, pop, 256);
+    std::printf("%d %d %d %d %zu %d %d %d %d %d %zu\n", p.S, p.Q,
+                2 * (p.lds + kStaticLds) <= kLdsPerCu ? 2 : 1, p.n_groups, p.lds, (int)p.cls, (int)t.use,
+                t.S, t.use ? (sets + t.spb - 1) / t.spb : 0, t.spb * t.n_wt, t.lds);
   }
 }
