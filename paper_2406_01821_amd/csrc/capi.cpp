@@ -79,42 +79,77 @@ void set_regions(DatasetRec &d, const int64_t *counts) {
 // lane and set chunks of Q, in CU microseconds of an average population.  A
 // block stages its tile (nf * 64 * S floats, 4 / S times), then its 16 waves
 // share the chunk's rule sets; two blocks share a CU where their LDS fits
-// twice.  The second one hides the latency of the record loads and LDS
-// reads at the price of 1.48 times longer visits, and fewer samples per lane
-// make a visit 0.66 (two) or 0.61 (one) of its length for a half or a quarter
-// of the samples.  What a grid costs beyond its work is its last round of
-// blocks: up to one round a launch lasts one block, just above one it lasts
-// two, and each further round adds one (0.6: the mean of a round's start and
-// end, where blocks do not run in step).
-double hard_cost(const DatasetRec &ds, int64_t n_sets, int n_cu, int S, int64_t Q, int per_cu) {
+// twice, which hides the latency of the record loads and LDS reads at the price
+// of 1.53 times longer visits; fewer samples per lane make a visit 0.59 (two)
+// or 0.87 (one) of its length for a half or a quarter of the samples.  What a
+// grid costs beyond its work is its last round of blocks: up to one round a
+// launch lasts one block (the slowest of those that share a CU, 1.07 mean
+// ones), just above one 1.69, and each further round adds one (0.44: the mean
+// of a round's start and end, where blocks do not run in step).
+double hard_cost(const DatasetRec &ds, int64_t n_sets, int n_cu, int S, int64_t Q) {
+  const int per_cu = 2 * (hard_block_lds(ds.nf, S, (int)Q, ds.nc, true) + kStaticLds) <= kLdsPerCu ? 2 : 1;
   const double blocks = (double)std::max<int64_t>(ds.n_tiles, 1) * (double)((n_sets + Q - 1) / Q);
   const double rounds = blocks / ((double)n_cu * per_cu);
-  const double on_cu = blocks > n_cu ? per_cu : 1;  // of the CU that is done last
-  const double stage = 3.6 + 0.058 * (ds.nf * 0.25 * S);  // latency, then KiB at 18 GB/s
-  const double visit = 1.39 * (on_cu > 1 ? 1.475 : 1.0) * (S == 4 ? 1.0 : S == 2 ? 0.66 : 0.61);
-  const double block = (4 / S) * (stage + std::max(1.0, (double)Q / 16 + 0.5) * visit);
-  return block * (rounds <= 1 ? 1.0 : rounds < 1.4 ? 2.0 : rounds + 0.6);
+  const bool shared = blocks > n_cu && per_cu == 2;  // the CU that is done last
+  const double stage = 2.2 + 0.061 * (ds.nf * 0.25 * S);  // latency, then KiB at 16 GB/s
+  const double visit = 1.6 * (shared ? 1.525 : 1.0) * (S == 4 ? 1.0 : S == 2 ? 0.59 : 0.87);
+  const double block = (4 / S) * (stage + std::max(1.0, (double)Q / 16 + 0.34) * visit);
+  const double turns = rounds <= 1 ? (shared ? 1.07 : 1.0) : std::max(rounds + 0.44, 1.69);
+  return block * turns + 0.06 * blocks / n_cu;
+}
+
+// The plain choice that hard_config starts from: the most samples per lane that
+// leave room for two blocks per CU with a chunk of at least 64 sets (with no
+// such S, the most that fit one block), the largest chunk that keeps them, and
+// chunks halved (down to 64 sets, 32 on tables of at most four tiles) until
+// there are four blocks per CU; equal chunks.
+void hard_plain_config(const DatasetRec &ds, int64_t sets, int n_cu, int *S, int64_t *Q) {
+  const int64_t tiles = std::max<int64_t>(ds.n_tiles, 1);
+  const int64_t q_floor = tiles <= 4 ? 32 : 64;
+  const size_t half = kLdsPerCu / 2 - kStaticLds;
+  const auto lds = [&](int s, int64_t q) { return hard_block_lds(ds.nf, s, (int)q, ds.nc, true); };
+  int64_t q = std::min<int64_t>(sets, kHardChunkMax);
+  const int64_t q_min = std::min<int64_t>(q, 64);
+  int s = 4;
+  while (s > 1 && lds(s, q_min) > half) s >>= 1;
+  size_t budget = half;
+  if (lds(s, q_min) > half) {
+    s = 4;
+    while (s > 1 && (size_t)ds.nf * 256 * s > 150 * 1024) s >>= 1;
+    budget = kDynLdsMax;
+  }
+  while (q > 1 && lds(s, q) > budget) q = (q + 1) / 2;
+  while (q > q_floor && (sets + q - 1) / q * tiles < 4LL * n_cu) q = (q + 1) / 2;
+  const int64_t chunks = (sets + q - 1) / q;
+  *S = s;
+  *Q = (sets + chunks - 1) / chunks;
 }
 
 // Launch configuration of the plain hard-eval path: over single-tile groups,
 // the samples per lane and the chunk of rule sets that hard_cost finds
 // cheapest, among the fewest chunks that the LDS allows (at one or two blocks
 // per CU), up to three more, and those that fill the GPU's workgroup slots
-// once to four times.  The
-// constants of hard_cost were fitted to 39 tables of 3 to 3908 tiles with 20
-// to 300 features and 30 to 4096 rule sets, each timed over its S and Q: its
-// choice is on average 2% (at most 18%) slower than the best of them, where
-// the previous rule (two blocks per CU whenever any S allows it, 4 * n_cu
-// blocks) was 16% slower on average: 50 021 x 97 features x 377 sets 71 us
-// against 129 us, 20 000 x 110 x 3000 118 against 171 us.  Chunks hold at
-// least 32 rule sets, two per wave of a block, on tables of at most four
-// tiles, and 16 on larger ones.
+// once to four times; hard_plain_config's unless another one is estimated at
+// less than 0.98 of it, since the population's own rules are not looked at.
+// The constants of hard_cost were fitted to 208 tables of 3 to 3908 tiles with 2
+// to 400 features and 8 to 4096 rule sets of 1 to 550 conditions, each timed
+// over its S and Q (profiles/hard_plan_timings.txt): the choice is 1.1% slower
+// than the best of them on average (24% at most) and takes 0.90 of
+// hard_plain_config's time, at most 1.04 on any; over 516 other shapes 0.82 of
+// it (84 016 x 79 features x 1978 sets of 1 to 14 rules 233 us against 326).
+// Chunks hold at least 32 rule sets, two per wave of a block, on tables of at
+// most four tiles, and 16 on larger ones.
 void hard_config(const DatasetRec &ds, int32_t n_sets, int n_cu, int *S, int *Q, int *TG) {
   const int64_t tiles = std::max<int64_t>(ds.n_tiles, 1);
   const int64_t sets = std::max<int32_t>(n_sets, 1);
   const int64_t q_floor = std::min<int64_t>(sets, tiles <= 4 ? 32 : 16);
-  double best = 0;
+  int64_t plain_q;
   *S = 0;
+  hard_plain_config(ds, sets, n_cu, S, &plain_q);
+  *Q = (int)plain_q;
+  const bool fits = hard_block_lds(ds.nf, *S, *Q, ds.nc, true) <= kDynLdsMax;
+  double best = fits ? 0.98 * hard_cost(ds, sets, n_cu, *S, plain_q) : 0;
+  if (!fits) *S = 0;
   for (int s = 4; s >= 1; s >>= 1) {
     for (int per_cu = 2; per_cu >= 1; --per_cu) {
       const size_t budget = per_cu == 2 ? kLdsPerCu / 2 - kStaticLds : kDynLdsMax;
@@ -129,7 +164,7 @@ void hard_config(const DatasetRec &ds, int32_t n_sets, int n_cu, int *S, int *Q,
         const int64_t chunks =
             k < 4 ? fewest + k : std::max(fewest, (int64_t)(k - 3) * n_cu * per_cu / tiles);
         const int64_t q = std::min(q_max, std::max(q_floor, (sets + chunks - 1) / chunks));
-        const double cost = hard_cost(ds, sets, n_cu, s, q, per_cu);
+        const double cost = hard_cost(ds, sets, n_cu, s, q);
         if (*S == 0 || cost < best) {
           best = cost;
           *S = s;
