@@ -646,7 +646,7 @@ aerl_status aerl_predict(aerl_ctx *ctx, int32_t pop_id, int32_t set, const float
   if (n < 0 || n > INT32_MAX) return fail(ctx, AERL_EINVAL, "n = %lld outside [0, 2^31)", (long long)n);
   if (n > 0 && (!rows || !pred)) return fail(ctx, AERL_EINVAL, "rows or pred is NULL");
   AERL_HIP(ctx, hipSetDevice(ctx->device));
-  AERL_HIP(ctx, launch_predict(pop, set, rows, n, pred, stream));
+  AERL_HIP(ctx, launch_predict(pop, set, rows, n, ctx->n_cu, pred, stream));
   return AERL_OK;
 }
 

@@ -284,13 +284,26 @@ __device__ __forceinline__ void ldc_pair(const int4 *p, int4 (&out)[2]) {
   "v_mov_b32 %[vt], %[t0]\n"                            \
   AERL_ADD_CLASS_V(W)
 
+// Prediction (S = 4 only): lanes set in the masks M_i take the class in W (pred_i).
+#define AERL_SET_CLASS_4(W, M0, M1, M2, M3)             \
+  "v_bfe_u32 %[vt], " W ", 12, 6\n"                     \
+  "v_cndmask_b32_e64 %[p0], %[p0], %[vt], " M0 "\n"     \
+  "v_cndmask_b32_e64 %[p1], %[p1], %[vt], " M1 "\n"     \
+  "v_cndmask_b32_e64 %[p2], %[p2], %[vt], " M2 "\n"     \
+  "v_cndmask_b32_e64 %[p3], %[p3], %[vt], " M3 "\n"
+#define AERL_SETC_4F(W) AERL_SET_CLASS_4(W, "s[56:57]", "s[58:59]", "s[60:61]", "s[62:63]")
+#define AERL_SETC_4U(W) AERL_SET_CLASS_4(W, "%[u0]", "%[u1]", "%[u2]", "%[u3]")
+
 // The rule of the (last) record in W fires for the lanes in f: count them
-// for its class and retire them (to ALIVE, or on with SCC = some lane still
-// undecided).
-#define AERL_COMMIT(S, W, ALIVE) \
+// for its class (COUNT) or give them its class (PRED), and retire them (to
+// ALIVE, or on with SCC = some lane still undecided).
+#define AERL_COMMIT_COUNT(S, W, ALIVE) \
   AERL_CAT(AERL_POPC_, AERL_SM(S, F)) AERL_ADD_CLASS_V(W) AERL_CAT(AERL_RETIRE_, S)(ALIVE)
+#define AERL_COMMIT_PRED(S, W, ALIVE) \
+  AERL_CAT(AERL_SETC_, AERL_SM(S, F))(W) AERL_CAT(AERL_RETIRE_, S)(ALIVE)
 // An always-true rule in W decides every undecided lane.
-#define AERL_ALWAYS(S, W) AERL_CAT(AERL_POPC_, AERL_SM(S, U)) AERL_ADD_CLASS(W)
+#define AERL_ALWAYS_COUNT(S, W) AERL_CAT(AERL_POPC_, AERL_SM(S, U)) AERL_ADD_CLASS(W)
+#define AERL_ALWAYS_PRED(S, W) AERL_CAT(AERL_SETC_, AERL_SM(S, U))(W)
 
 // Start of a record whose row is at byte offset XX: read the row; records
 // with a flag in MASK go to SPEC; falls through (row waited for) with a fast
@@ -440,10 +453,10 @@ __device__ __forceinline__ void ldc_pair(const int4 *p, int4 (&out)[2]) {
   "s_cbranch_scc1 .Lnext_%=\n"                          \
   "s_branch .Ldone_%=\n"
 
-// The whole walk for S samples per lane.  Labels:
+// The whole walk for S samples per lane; KIND is COUNT or PRED.  Labels:
 // s/n = a rule starts / continues at the record, a/b = quad A / B, _le = the
 // <= direction (taken from a rule's first <= record to its end).
-#define AERL_WALK(S, WAY, SP)                                            \
+#define AERL_WALK(S, KIND, WAY, SP)                                            \
   AERL_CAT(AERL_START_, WAY)                                               \
   /* load the pair (o, o+16) into A, B; a rule starts at A */              \
   ".Lload_%=:\n"                                                           \
@@ -568,7 +581,7 @@ __device__ __forceinline__ void ldc_pair(const int4 *p, int4 (&out)[2]) {
   "s_bitcmp1_b32 s67, 11\n"                                                \
   "s_cbranch_scc0 .Lnb_%=\n"                                               \
   ".Lwa_%=:\n"                                                             \
-  AERL_COMMIT(S, "s67", AERL_CAT(AERL_NXA_, WAY))         \
+  AERL_CAT(AERL_COMMIT_, KIND)(S, "s67", AERL_CAT(AERL_NXA_, WAY))         \
   "s_cbranch_scc1 " AERL_CAT(AERL_NXA_, WAY) "\n"                          \
   "s_branch .Ldone_%=\n"                                                   \
   /* after a special record in B, or a rule's last record in B */          \
@@ -582,16 +595,16 @@ __device__ __forceinline__ void ldc_pair(const int4 *p, int4 (&out)[2]) {
   "s_bitcmp1_b32 s71, 11\n"                                                \
   "s_cbranch_scc0 .Llna_load_%=\n"                                         \
   ".Lwb_%=:\n"                                                             \
-  AERL_COMMIT(S, "s71", AERL_CAT(AERL_CBL_, WAY))         \
+  AERL_CAT(AERL_COMMIT_, KIND)(S, "s71", AERL_CAT(AERL_CBL_, WAY))         \
   AERL_CAT(AERL_NXB_, WAY)                                                 \
   /* an always-true rule decides every undecided lane */                   \
   ".Lalwa_%=:\n"                                                           \
   "s_waitcnt lgkmcnt(0)\n"                                                 \
-  AERL_ALWAYS(S, "s67")                                   \
+  AERL_CAT(AERL_ALWAYS_, KIND)(S, "s67")                                   \
   "s_branch .Ldone_%=\n"                                                   \
   ".Lalwb_%=:\n"                                                           \
   "s_waitcnt lgkmcnt(0)\n"                                                 \
-  AERL_ALWAYS(S, "s71")                                   \
+  AERL_CAT(AERL_ALWAYS_, KIND)(S, "s71")                                   \
   ".Ldone_%=:\n"
 
 #define AERL_WALK_CLOBBERS                                                 \
@@ -625,7 +638,7 @@ __device__ __forceinline__ int eval_set_count(uint32_t lds_lane, int lane, int4 
     uint64_t m;                                                                               \
     uint32_t o, t0, vt, vt2;                                                                  \
     int acc = 0;                                                                              \
-    asm volatile(AERL_WALK(S, SEQ, SP)                                                 \
+    asm volatile(AERL_WALK(S, COUNT, SEQ, SP)                                                 \
                  : AERL_COUNT_OUTS_##S, AERL_TEMPS                                            \
                  : [base] "s"(base), [lds] "v"(lds_lane), [lane] "v"(lane)                    \
                  : AERL_WALK_CLOBBERS);                                                       \
@@ -640,7 +653,7 @@ __device__ __forceinline__ int eval_set_count(uint32_t lds_lane, int lane, int4 
     uint64_t m;                                                                               \
     uint32_t o, t0, vt, vt2;                                                                  \
     int acc = 0;                                                                              \
-    asm volatile(AERL_WALK(S, FLT, SP)                                                 \
+    asm volatile(AERL_WALK(S, COUNT, FLT, SP)                                                 \
                  : AERL_COUNT_OUTS_##S, AERL_TEMPS, [mk] "+s"(mk)                             \
                  : [base] "s"(base), [lds] "v"(lds_lane), [lane] "v"(lane), [vst] "v"(vst)    \
                  : AERL_WALK_CLOBBERS);                                                       \
@@ -653,5 +666,23 @@ AERL_COUNT_SPECIALIZE(1, false, N)
 AERL_COUNT_SPECIALIZE(4, true, C)
 AERL_COUNT_SPECIALIZE(2, true, C)
 AERL_COUNT_SPECIALIZE(1, true, C)
+
+// Prediction form of the sequential walk, four samples per lane: pred[s]
+// receives the class of each lane's samples in vm (others keep their value).
+__device__ __forceinline__ void eval_set_pred4(uint32_t lds_lane, int4 set,
+                                               const uint4 *__restrict__ stream,
+                                               const uint64_t (&vm)[4], int (&pred)[4]) {
+  const uint4 *base = stream + set.x;
+  AERL_U_4
+  uint64_t m;
+  uint32_t o, t0, vt, vt2;
+  int p0 = pred[0], p1 = pred[1], p2 = pred[2], p3 = pred[3];
+  asm volatile(AERL_WALK(4, PRED, SEQ, C)
+               : [p0] "+v"(p0), [p1] "+v"(p1), [p2] "+v"(p2), [p3] "+v"(p3), [u0] "+s"(u0),
+                 [u1] "+s"(u1), [u2] "+s"(u2), [u3] "+s"(u3), AERL_TEMPS
+               : [base] "s"(base), [lds] "v"(lds_lane)
+               : AERL_WALK_CLOBBERS);
+  pred[0] = p0; pred[1] = p1; pred[2] = p2; pred[3] = p3;
+}
 
 }  // namespace aerl

@@ -326,6 +326,15 @@ __global__ __launch_bounds__(kPredictBlock) void k_predict(const float *__restri
                    (int64_t)blockIdx.x * kPredictRows * S, xs, first);
 }
 
+// The same, a wave per 256 rows that walks the rules in turn.
+__global__ __launch_bounds__(64) void k_predict_walk(const float *__restrict__ rows, int64_t n, int32_t nf,
+                                                     const int4 *__restrict__ sets, int32_t set_idx,
+                                                     const uint4 *__restrict__ conds,
+                                                     int32_t *__restrict__ out) {
+  extern __shared__ __align__(16) float xs[];  // [nf][256]
+  predict_walk(rows, n, nf, ldc(sets, set_idx), conds, out, (int64_t)blockIdx.x * 256, xs);
+}
+
 template <int S>
 hipError_t hard_dispatch(const HardArgs &a, dim3 grid, size_t lds, bool cat, bool c10,
                          hipStream_t st) {
@@ -425,26 +434,36 @@ hipError_t launch_hard_reduce(const HardLaunch &h, int n_cu, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_predict(const PopRec &pop, int32_t set, const float *rows, int64_t n,
+hipError_t launch_predict(const PopRec &pop, int32_t set, const float *rows, int64_t n, int n_cu,
                           int32_t *pred, hipStream_t st) {
   if (n <= 0) return hipSuccess;
+  // A wave per 256 rows that walks the rules in turn, where rows alone fill the
+  // GPU and little is staged for each: over 14 rule sets of 1 to 96 rules it
+  // takes 0.88 of the blocks' time on 1 to 5 features from 2^15 rows (7.5 us
+  // both below), 0.5 to 0.7 from 2^20 (2^21 x 5, 24 rules 18 us against 40), and
+  // 0.84 on 6 to 9 features from 5 * 2^18 (2^21 x 8 31 us against 38, 1572864 x
+  // 6 0.52).  On fewer rows of those (2^20 x 8 1.09) and on more features (2^21
+  // x 10 1.10, x 12 1.22, x 32 3.3) it is the slower one.
+  if (pop.nf <= 5 ? n >= (1 << 15) : pop.nf <= 9 && n >= (5 << 18)) {
+    hipLaunchKernelGGL(k_predict_walk, dim3((unsigned)((n + 255) / 256)), dim3(64),
+                       predict_walk_lds(pop.nf), st, rows, n, pop.nf, pop.sets, set, pop.hconds, pred);
+    return hipGetLastError();
+  }
   // Four rows per lane once 64-row blocks would fill the GPU several times
-  // over, on tables narrow enough to keep 16 waves per CU (2^20 rows x 8
-  // features, 32 rules: 42 us with one row per lane, 23 with four; x 32
-  // features 62 us, one wave per 256 rows walking every rule took 202).
+  // over, on tables narrow enough to keep 16 waves per CU (2^20 rows x 32
+  // features 62 us; one wave per 256 rows walking every rule 178).
   const int S = n >= kPredictWideRows && pop.nf <= kPredictWideFeatures ? 4 : 1;
   const size_t lds = predict_lds(pop.nf, S);
   const int64_t blocks = (n + kPredictRows * S - 1) / (kPredictRows * S);
   if (lds > kDynLdsMax) return hipErrorInvalidValue;
   // A wave per rule while all blocks are resident at once (latency: 4096 rows
-  // x 64 features 9.3 us).  Larger requests take fewer waves per block, whose
+  // x 64 features 9.1 us).  Larger requests take fewer waves per block, whose
   // walks end once every row is decided, but enough for 16 per CU under the
   // LDS of their rows.
-  constexpr int64_t kResidentWaves = 256 * 32;
   int waves = 1, least = 1;
   while (waves < kPredictBlock / 64 && waves < std::max(pop.max_rules, 4)) waves *= 2;
   while (least < 16 && least * (int)(kLdsPerCu / lds) < 16) least *= 2;
-  while (waves > least && blocks * waves > kResidentWaves) waves /= 2;
+  while (waves > least && blocks * waves > 32LL * n_cu) waves /= 2;
   const dim3 grid((unsigned)blocks), block((unsigned)waves * 64);
   if (S == 4)
     hipLaunchKernelGGL(k_predict<4>, grid, block, lds, st, rows, n, pop.nf, pop.sets, set, pop.hconds,

@@ -255,7 +255,7 @@ inline int64_t hard_block_count(const DatasetRec &ds, int sets_per_chunk, int32_
   return chunks * hard_group_count(ds, tiles_per_group);
 }
 
-hipError_t launch_predict(const PopRec &pop, int32_t set, const float *rows, int64_t n,
+hipError_t launch_predict(const PopRec &pop, int32_t set, const float *rows, int64_t n, int n_cu,
                           int32_t *pred, hipStream_t s);
 
 // Upload (layout.hip): rows per group of the grouping pass, groups, and
