@@ -98,9 +98,13 @@ struct PredictTask {
   const uint4 *conds; // device record stream of its population
   int32_t *out;       // device [n]
   int64_t n, row0;    // rows of the request, first row of this task
-  int32_t heads;      // its head table, in records from conds
+  uint32_t heads;     // its head table, in records from conds
   int16_t nf, S;
 };
+// Up to 2^31 records of 16 bytes and as many words lie between the two.
+inline uint32_t heads_from_conds(const PackedLayout &L) {
+  return (uint32_t)((L.heads_off - L.hconds_off) / sizeof(uint4));
+}
 struct PredictLaunch {
   const PredictTask *tasks;
   int32_t n_tasks;

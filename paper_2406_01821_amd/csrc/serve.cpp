@@ -196,7 +196,7 @@ bool Serve::launch_one(std::unique_lock<std::mutex> &lk, Slot &slot) {
         t.out = reinterpret_cast<int32_t *>(dev + r->out_off);
         t.n = r->n_rows;
         t.row0 = row0;
-        t.heads = (int32_t)(dheads - dconds);
+        t.heads = heads_from_conds(r->L);
         t.nf = (int16_t)r->nf;
         t.S = (int16_t)S;
         ptasks.push_back(t);
