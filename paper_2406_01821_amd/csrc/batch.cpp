@@ -147,8 +147,6 @@ void emit_batch_tables(const BatchTables &b, void *img, char *dev, int n_cu, Bat
   bl->grid = std::max<int64_t>(1, std::min<int64_t>((int64_t)n_cu * per_cu, (int64_t)b.tasks.size()));
 }
 
-int predict_task_tiles(int32_t nf) { return (size_t)nf * 256 * 4 <= kDynLdsMax ? kPredictTaskTiles : 1; }
-
 namespace {
 
 struct ItemView {

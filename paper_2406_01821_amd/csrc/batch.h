@@ -89,9 +89,10 @@ int64_t batch_task_count(const DatasetRec &ds, int32_t n_sets, const BatchSplit 
 // CUs, never more blocks than work items).
 void emit_batch_tables(const BatchTables &t, void *img, char *dev, int n_cu, BatchLaunch *l);
 
-// Prediction work of a batch: a task is S x 64 rows of one request, a block
-// for each 64.
+// Prediction work of a batch: a task is kPredictTaskTiles x 64 rows of one
+// request, a block for each 64.
 constexpr int kPredictTaskTiles = 4;
+constexpr int64_t kPredictTaskRows = kPredictTaskTiles * 64;
 struct PredictTask {
   const float *rows;  // device [n][nf] row-major
   const int4 *set;    // device set record of the rule set to apply
@@ -99,7 +100,7 @@ struct PredictTask {
   int32_t *out;       // device [n]
   int64_t n, row0;    // rows of the request, first row of this task
   uint32_t heads;     // its head table, in records from conds
-  int16_t nf, S;
+  int32_t nf;
 };
 // Up to 2^31 records of 16 bytes and as many words lie between the two.
 inline uint32_t heads_from_conds(const PackedLayout &L) {
@@ -111,6 +112,5 @@ struct PredictLaunch {
   size_t lds;
 };
 hipError_t launch_predict_batch(const PredictLaunch &p, hipStream_t st);
-int predict_task_tiles(int32_t nf);  // S of a task: 4, or 1 for wide tables
 
 }  // namespace aerl

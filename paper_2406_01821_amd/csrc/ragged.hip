@@ -73,7 +73,7 @@ __global__ __launch_bounds__(kPredictBatchBlock) void k_predict_batch(
   __shared__ int32_t first[kPredictRows];
   const PredictTask t = tasks[blockIdx.x];
   const int64_t row0 = t.row0 + (int64_t)blockIdx.y * kPredictRows;
-  if ((int)blockIdx.y >= t.S || row0 >= t.n) return;  // the whole block
+  if (row0 >= t.n) return;  // the whole block
   predict_block<1>(t.rows, t.n, t.nf, ldc(t.set, 0), t.conds, t.conds + t.heads, t.out, row0, xs,
                    first);
 }

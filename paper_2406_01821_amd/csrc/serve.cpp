@@ -186,9 +186,8 @@ bool Serve::launch_one(std::unique_lock<std::mutex> &lk, Slot &slot) {
       src.push_back({r->ds, r->rec.n_sets, reinterpret_cast<const int4 *>(r->image.data()), dsets,
                      dconds, dheads, c, cf, r->rec.n_cat > 0});
     } else {
-      const int S = predict_task_tiles(r->nf);
       plds = std::max(plds, predict_lds(r->nf));
-      for (int64_t row0 = 0; row0 < r->n_rows; row0 += kPredictRows * S) {
+      for (int64_t row0 = 0; row0 < r->n_rows; row0 += kPredictTaskRows) {
         PredictTask t{};
         t.rows = reinterpret_cast<const float *>(dev + r->rows_off);
         t.set = dsets + r->set_index;
@@ -197,8 +196,7 @@ bool Serve::launch_one(std::unique_lock<std::mutex> &lk, Slot &slot) {
         t.n = r->n_rows;
         t.row0 = row0;
         t.heads = heads_from_conds(r->L);
-        t.nf = (int16_t)r->nf;
-        t.S = (int16_t)S;
+        t.nf = r->nf;
         ptasks.push_back(t);
       }
     }
@@ -524,8 +522,7 @@ aerl_status aerl_serve_submit(aerl_ctx *ctx, const aerl_request *req, uint64_t *
     if (r->n_rows > 0) r->rows.assign(req->rows, req->rows + (size_t)r->n_rows * r->nf);
     r->in_bytes = al(r->L.total) + al((size_t)r->n_rows * r->nf * 4);
     r->out_bytes = al((size_t)r->n_rows * 4);
-    const int S = predict_task_tiles(r->nf);
-    r->table_bytes = (size_t)((r->n_rows + kPredictRows * S - 1) / (kPredictRows * S)) * sizeof(PredictTask);
+    r->table_bytes = (size_t)((r->n_rows + kPredictTaskRows - 1) / kPredictTaskRows) * sizeof(PredictTask);
     r->nominal = (double)r->n_rows * (double)hsets[r->set_index].w;
   }
   std::lock_guard<std::recursive_mutex> lk(ctx->mu);
