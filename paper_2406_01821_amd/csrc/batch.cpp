@@ -277,11 +277,11 @@ std::array<int32_t, 3> default_split(const std::vector<ItemView> &v, int n_cu, c
 }
 
 // The caller's split, with zero fields taken from the tuned table for this
-// batch shape or the planned default.  *plain, when given: the split with 512
-// sets by one tile for the fields that neither gives, whose workspace a caller
-// may have instead.
+// batch shape or the planned default.  *plain: the split with 512 sets by one
+// tile for the fields that neither gives, whose workspace a caller may have
+// instead.
 aerl_status resolve_split(aerl_ctx *ctx, const std::vector<ItemView> &v, const aerl_batch_cfg *cfg,
-                          BatchSplit *sp, BatchSplit *plain = nullptr) {
+                          BatchSplit *sp, BatchSplit *plain) {
   load_tune_file(ctx);
   auto it = ctx->tuned.find(shape_key(v));
   const std::array<int32_t, 3> d =
@@ -295,18 +295,19 @@ aerl_status resolve_split(aerl_ctx *ctx, const std::vector<ItemView> &v, const a
   sp->Q = q;
   sp->TG = tg;
   sp->tile_budget = (size_t)kib * 1024;
-  if (plain) {
-    *plain = *sp;
-    if (it == ctx->tuned.end()) {
-      if (!cfg || cfg->sets_per_task == 0) plain->Q = 512;
-      if (!cfg || cfg->tiles_per_task == 0) plain->TG = 1;
-    }
+  *plain = *sp;
+  if (it == ctx->tuned.end()) {
+    if (!cfg || cfg->sets_per_task == 0) plain->Q = 512;
+    if (!cfg || cfg->tiles_per_task == 0) plain->TG = 1;
   }
-  // work items are counted and indexed with int32 on the device
-  int64_t tasks = 0;
-  for (const auto &e : v) tasks += batch_task_count(*e.ds, e.pop->n_sets, *sp);
-  if (tasks > INT32_MAX)
-    return fail(ctx, AERL_EINVAL, "%lld work items exceed 2^31 - 1; raise tiles_per_task", (long long)tasks);
+  int64_t tasks = 0, plain_tasks = 0;
+  for (const auto &e : v) {
+    tasks += batch_task_count(*e.ds, e.pop->n_sets, *sp);
+    plain_tasks += batch_task_count(*e.ds, e.pop->n_sets, *plain);
+  }
+  if (!settle_split(tasks, *plain, plain_tasks, sp))
+    return fail(ctx, AERL_EINVAL, "%lld work items exceed 2^31 - 1; raise tiles_per_task",
+                (long long)plain_tasks);
   return AERL_OK;
 }
 

@@ -48,6 +48,16 @@ struct BatchSplit {
   size_t tile_budget = 64 * 1024;
 };
 
+// Whether a batch under split *sp, of `tasks` work items, or else under
+// `plain`, of plain_tasks, can be launched: items are counted and indexed with
+// int32 on the device.  A batch whose plain split has too many is refused; one
+// whose *sp alone has takes the plain one.
+inline bool settle_split(int64_t tasks, const BatchSplit &plain, int64_t plain_tasks, BatchSplit *sp) {
+  if (plain_tasks > INT32_MAX) return false;
+  if (tasks > INT32_MAX) *sp = plain;
+  return true;
+}
+
 // Samples per lane of an item with nf features: the most of {4, 2, 1} whose
 // 64-lane tile of all features fits the budget.
 int batch_samples_per_lane(int32_t nf, size_t tile_budget);
