@@ -16,6 +16,7 @@
 #include <sstream>
 
 #include "batch.h"
+#include "batch_plan.h"
 
 namespace aerl {
 
@@ -36,26 +37,8 @@ void destroy_plan(BatchPlanRec *p) {
   delete p;
 }
 
-int batch_samples_per_lane(int32_t nf, size_t tile_budget) {
-  int s = 4;
-  while (s > 1 && (size_t)nf * 256 * s > tile_budget) s >>= 1;
-  return s;
-}
-
 namespace {
 size_t align256_(size_t v) { return (v + 255) & ~size_t(255); }
-}  // namespace
-
-namespace {
-int32_t sets_per_item(const DatasetRec &ds, int32_t n_sets, const BatchSplit &sp) {
-  const int32_t Q = sp.Q;
-  const size_t tile_bytes = (size_t)ds.nf * 64 * batch_samples_per_lane(ds.nf, sp.tile_budget) * 4;
-  const int32_t q_fit =
-      (int32_t)std::min<size_t>((kBatchLdsMax - tile_bytes - (size_t)ds.nf * 8 - 4) /
-                                    ((size_t)std::max(hard_counters_per_set(ds.nc), 1) * 2),
-                                1 << 20);
-  return std::max(1, std::min({Q, n_sets, q_fit}));
-}
 }  // namespace
 
 int64_t batch_task_count(const DatasetRec &ds, int32_t n_sets, const BatchSplit &sp) {
@@ -149,12 +132,6 @@ void emit_batch_tables(const BatchTables &b, void *img, char *dev, int n_cu, Bat
 
 namespace {
 
-struct ItemView {
-  const DatasetRec *ds;
-  const PopRec *pop;
-  const aerl_batch_item *item;
-};
-
 aerl_status gather(aerl_ctx *ctx, const aerl_batch_item *items, int32_t n, std::vector<ItemView> *out) {
   if (n < 0 || (n > 0 && !items)) return fail(ctx, AERL_EINVAL, "bad item list");
   out->clear();
@@ -208,72 +185,6 @@ void load_tune_file(aerl_ctx *ctx) {
   int32_t q, tg, kib;
   double ms;
   while (in >> key >> q >> tg >> kib >> ms) ctx->tuned[key] = {q, tg, kib};
-}
-
-// Estimated time (us) of a batch under a split.  A work item costs its pull,
-// records and flush (20), and per wave tile the staging (latency and KiB) and
-// the walks of its 16 waves at two blocks per CU.  The list is pulled longest
-// first, so it ends a part of a mean item after an even share of the work,
-// or with its longest items.
-double split_cost(const std::vector<ItemView> &v, const BatchSplit &sp, int n_cu) {
-  double total = 0, longest = 0;
-  int64_t n = 0;
-  size_t lds = 0;
-  for (const auto &e : v) {
-    const DatasetRec &ds = *e.ds;
-    const int32_t sets = e.pop->n_sets;
-    if (sets <= 0 || ds.n_tiles == 0) continue;
-    const int S = batch_samples_per_lane(ds.nf, sp.tile_budget);
-    const int32_t q = sets_per_item(ds, sets, sp);
-    lds = std::max(lds, hard_block_lds(ds.nf, S, q, ds.nc));
-    const double stage = 1.5 + 0.08 * (ds.nf * 0.25 * S);
-    const double visit = S == 4 ? 3.5 : S == 2 ? 3.0 : 2.7;
-    const auto cost = [&](int32_t q1, int32_t tiles) {
-      return 20 + tiles * (4 / S) * (stage + std::max(1.0, q1 / 16.0 + 0.5) * visit);
-    };
-    const auto add = [&](int64_t groups, int32_t tiles) {
-      if (groups == 0 || tiles == 0) return;
-      total += groups * (double)(sets / q) * cost(q, tiles);
-      if (sets % q) total += groups * cost(sets % q, tiles);
-      n += groups * ((sets + q - 1) / q);
-      longest = std::max(longest, cost(q, tiles));
-    };
-    for (int c = 0; c < ds.nc; ++c) {
-      add(ds.region_tiles[c] / sp.TG, sp.TG);
-      add(1, ds.region_tiles[c] % sp.TG);
-    }
-  }
-  const double slots = (double)n_cu * (2 * (lds + kStaticLds) <= kLdsPerCu ? 2 : 1);
-  if ((double)n <= slots) return longest;
-  const double share = total / slots;
-  return std::max(share + 0.72 * total / n, std::pow(std::pow(share, 3.7) + std::pow(longest, 3.7), 1 / 3.7));
-}
-
-// The split that split_cost finds cheapest, of 32 to 512 rule sets by one or
-// two tiles, at the fields that are not given (> 0).  Over 36 batches of 3 to
-// 64 runs of 300 to 200 000 rows, each timed over its splits, the choice is 1%
-// slower than the best one on average (512 sets by one tile for all: 17%):
-// 6 runs of at most 3000 rows 39 us against 108, 13 runs of 1500 to 68 000 rows
-// 84 against 112, 24 runs of 1000 to 200 000 rows 637 against 655.
-std::array<int32_t, 3> default_split(const std::vector<ItemView> &v, int n_cu, const aerl_batch_cfg *cfg) {
-  const int32_t kib = cfg && cfg->tile_kib > 0 ? cfg->tile_kib : 64;
-  std::array<int32_t, 3> best = {512, 1, kib};
-  if (kib > (int32_t)(kBatchLdsMax / 1024)) return best;  // refused by the caller
-  double best_cost = 0;
-  for (int32_t q = 512; q >= 32; q /= 2) {
-    for (int32_t tg = 1; tg <= 2; ++tg) {
-      BatchSplit sp;
-      sp.Q = cfg && cfg->sets_per_task > 0 ? cfg->sets_per_task : q;
-      sp.TG = cfg && cfg->tiles_per_task > 0 ? cfg->tiles_per_task : tg;
-      sp.tile_budget = (size_t)kib * 1024;
-      const double cost = split_cost(v, sp, n_cu);
-      if (best_cost == 0 || cost < best_cost) {
-        best_cost = cost;
-        best = {sp.Q, sp.TG, kib};
-      }
-    }
-  }
-  return best;
 }
 
 // The caller's split, with zero fields taken from the tuned table for this

@@ -58,10 +58,6 @@ inline bool settle_split(int64_t tasks, const BatchSplit &plain, int64_t plain_t
   return true;
 }
 
-// Samples per lane of an item with nf features: the most of {4, 2, 1} whose
-// 64-lane tile of all features fits the budget.
-int batch_samples_per_lane(int32_t nf, size_t tile_budget);
-
 // One evaluation of a batch, as the table builder sees it.
 struct BatchSource {
   const DatasetRec *ds;

@@ -1,12 +1,13 @@
-"""Device tables of the batched paths at sizes past 32 bits, on the host:
-tests/sched/tables_driver.cpp checks the arithmetic of csrc/batch.h."""
+"""Device tables of the batched paths at sizes past 32 bits and the split that
+a batch gets, on the host: tests/sched/tables_driver.cpp checks the arithmetic
+of csrc/batch.h and csrc/batch_plan.h."""
 import os
 import subprocess
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def test_tables_past_32_bits(tmp_path):
+def test_tables_and_splits(tmp_path):
     exe = str(tmp_path / "tables_driver")
     r = subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I",
                         os.path.join(ROOT, "paper_2406_01821_amd", "csrc"), "-I",
