@@ -103,22 +103,27 @@ int sets_per_block(int n_sets, int64_t groups, int64_t target, int min_q) {
 // Whether a forward pass classifies.  Per tile it costs the extremes (a pass
 // over nf rows) and per rule set and 64 conditions a classification, and it
 // saves a share of the sweep that grows with the conditions of a rule (one out
-// of reach drops the rule).  Of 270 shapes timed both ways the line falls where
+// of reach drops the rule).  Of 439 shapes timed both ways the line falls where
 // a launch has 600,000 (tile, condition) pairs (60,000 x 32, 40 rule sets of 8
-// x 4 conditions: 45 us, plain 55; 262,144 x 32 x 1024 of 16 x 4: 3.0 and 6.5
-// ms); on wider tables, whose tiles are half or a quarter as long for the same
-// extremes, only with enough rule sets per block (30,000 x 90 x 200 of 8-16 x
-// 2-5: 190 and 180 us).  Smaller launches gain on narrow tables alone (40,000 x
-// 60, 16 rule sets: 37 and 28 us; 20,011 x 45, 150 of 1-24 x 1-6: 98 and 104),
-// by rules of more than two conditions or many of them per staged value (23,741
-// x 38, 32 of 24 x 2: 52 and 49 us).  Rules of more than 64 conditions are
-// swept in full in any case.
+// x 4 conditions: 45 us, plain 55; 262,144 x 32 x 1024 of 16 x 4: 2.8 and 6.5
+// ms), unless its rules hold one condition (253,611 x 53 x 1448 of 8 x 1: 4.1 and
+// 3.9 ms) or, short of four, a block sweeps too few for the features that it looks
+// over (96,217 x 32 x 533 of 2 x 2: 276 and 237 us); on wider tables, whose tiles
+// are half or a quarter as long for the same extremes, only with enough rule sets
+// per block (30,000 x 90 x 200 of 8-16 x 2-5: 190 and 180 us).  Smaller launches
+// gain on narrow tables alone (40,000 x 60, 16 rule sets: 37 and 28 us; 20,011 x
+// 45, 150 of 1-24 x 1-6: 98 and 104), by rules of more than two conditions or
+// many of them per staged value (23,741 x 38, 32 of 24 x 2: 52 and 49 us; 32,803
+// x 5, 3 of 50 x 1-2: 62 and 57).  Rules of more than 64 conditions are swept in
+// full in any case.
 bool forward_classifies(const DatasetRec &ds, const PopRec &pop, int sets_per_block) {
   if (ds.n_tiles < kClassifyTiles || pop.n_conds > 72LL * pop.n_rules) return false;
   const double per_block = (double)sets_per_block * pop.n_conds / std::max(pop.n_sets, 1);
-  if ((double)ds.n_tiles * pop.n_conds >= 6e5) return ds.nf <= 64 || per_block >= 8.0 * ds.nf;
+  const double per_rule = (double)pop.n_conds / std::max(pop.n_rules, 1);
+  if ((double)ds.n_tiles * pop.n_conds >= 6e5)
+    return per_rule >= 1.3 && per_block >= (ds.nf > 64 ? 8.0 : per_rule < 4 ? 3.5 : 0.0) * ds.nf;
   return ds.n_tiles >= 24 && ds.nf <= 52 && per_block >= 200 &&
-         (pop.n_conds >= 2.5 * pop.n_rules || per_block >= 12.0 * ds.nf);
+         (per_rule >= 2.5 || (per_rule >= 1.6 && per_block >= 12.0 * ds.nf));
 }
 
 SoftPlan plan_forward(const DatasetRec &ds, const PopRec &pop) {
