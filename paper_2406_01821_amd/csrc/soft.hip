@@ -299,8 +299,8 @@ __device__ __forceinline__ void tile_extremes(const float *xs, int nf, int valid
 // Thresholds drawn over a column's whole range lie, for most tiles, many tau
 // from all of its samples: on the 262,144 x 32 table with 1024 rule sets of
 // 16 rules x 4 conditions a forward pass is left with 42% of the rules and
-// 32% of the conditions (6.47 -> 3.01 ms), the adjoint with 62% and 54%
-// (17.2 -> 8.75 ms), the softmax head with 32% and 23%; results bit for bit
+// 32% of the conditions (6.47 -> 2.8 ms), the adjoint with 62% and 54%
+// (17.2 -> 8.2 ms), the softmax head with 32% and 23%; results bit for bit
 // the same.  Both kernels stay VALU-bound.
 constexpr float kDeadLoss = 180.0f;
 constexpr float kDeadProb = 128.0f;
@@ -1147,7 +1147,7 @@ __global__ __launch_bounds__(kSoftBlock) void k_smax_fwd(const SoftArgs a, float
   smax_fwd<S, NC, Acc, TONLY, false>(a, beta2);
 }
 
-template <int NC, class Acc>
+template <int NC, class Acc, bool TONLY>
 __global__ __launch_bounds__(kSmaxBwdWaves * 64) void k_smax_bwd(const SoftArgs a, float beta,
                                                                  float beta2) {
   constexpr int TS = 64, WPT = AERL_TILE / TS;
@@ -1233,8 +1233,12 @@ __global__ __launch_bounds__(kSmaxBwdWaves * 64) void k_smax_bwd(const SoftArgs 
         Acc ra;
         for (int j = r.x; j < r.x + r.y; ++j) {
           float z[1], xf[1], xg[1];
-          bool ff;
-          cond_z<1>(a, xs, lane, j, z, xf, xg, ff);
+          if constexpr (TONLY) {
+            cond_z_t<1>(a, xs, lane, j, z, xf, xg);
+          } else {
+            bool ff;
+            cond_z<1>(a, xs, lane, j, z, xf, xg, ff);
+          }
           const float t = ra.add(z[0]);
           // dL/dz = dL/dr_k * r_k * sigmoid(-z)
           const float dz = drk * acc_sig_neg(ra, a2k, z[0], t);
@@ -1518,10 +1522,16 @@ void launch_smax_bwd_nc(const SoftPlan &p, dim3 grid, hipStream_t st, const Soft
                         bool tonly, float beta, float beta2) {
   if (!p.reg) {
     const dim3 b(p.waves * 64);
-    if (prod)
-      hipLaunchKernelGGL((k_smax_bwd<NC, RuleProd>), grid, b, p.lds, st, a, beta, beta2);
+    // threshold rules alone spare a branch per condition (29,646 x 44, 111 rule
+    // sets of 80 rules: 9.9 ms against 10.4)
+    if (prod && tonly)
+      hipLaunchKernelGGL((k_smax_bwd<NC, RuleProd, true>), grid, b, p.lds, st, a, beta, beta2);
+    else if (prod)
+      hipLaunchKernelGGL((k_smax_bwd<NC, RuleProd, false>), grid, b, p.lds, st, a, beta, beta2);
+    else if (tonly)
+      hipLaunchKernelGGL((k_smax_bwd<NC, RuleAcc, true>), grid, b, p.lds, st, a, beta, beta2);
     else
-      hipLaunchKernelGGL((k_smax_bwd<NC, RuleAcc>), grid, b, p.lds, st, a, beta, beta2);
+      hipLaunchKernelGGL((k_smax_bwd<NC, RuleAcc, false>), grid, b, p.lds, st, a, beta, beta2);
     return;
   }
   if constexpr (NC <= 4) {
