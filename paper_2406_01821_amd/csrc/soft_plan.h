@@ -231,8 +231,20 @@ SoftPlan plan_backward(const DatasetRec &ds, const PopRec &pop) {
 
 int smax_nc(int nc) { return nc <= 2 ? 2 : nc <= 4 ? 4 : nc <= 8 ? 8 : 16; }
 
+// One or two rule sets of more than eight classes are a wave or two per block,
+// which one sample per lane leaves waiting for their private memory: their state
+// is kept in LDS where most wave tiles have samples (12 classes, one set of 33
+// rules: 2081 samples 160 us against 205, 9000 169 and 198; 500 samples 1.0
+// against 0.5, five sets 1.0 and 0.7 at any size).
 SoftPlan plan_smax_backward(const DatasetRec &ds, const PopRec &pop) {
-  return plan_adjoint(ds, pop, std::min(4, 16 / smax_nc(ds.nc)), kSmaxBwdWaves, 0);
+  const SoftPlan p = plan_adjoint(ds, pop, std::min(4, 16 / smax_nc(ds.nc)), kSmaxBwdWaves, 0);
+  if (p.reg && smax_nc(ds.nc) > 8 && pop.n_sets <= 2 && ds.n >= 128LL * ds.nc) {
+    SoftPlan own = p;
+    own.cls = false;
+    own = plan_lds_state(ds, pop, own, kSmaxBwdWaves);
+    if (own.lds <= kDynLdsMax) return own;
+  }
+  return p;
 }
 
 // Same groups (and so the same workspace) as the first-firing forward.  Four
