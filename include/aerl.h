@@ -467,7 +467,9 @@ aerl_status aerl_soft_forward(aerl_ctx *ctx, int32_t dataset_id, int32_t pop_id,
  * device fp32 [n_sets]; ws holds at least backward_bytes.  Deterministic.
  * Rule sets of up to 64 rules run with the per-rule state in per-lane
  * memory; longer ones keep it in LDS with fewer waves per workgroup as they
- * grow, which bounds them (about 300 rules with few features).  Errors:
+ * grow.  From 33 rules on a population is accepted while 256 bytes per
+ * feature, 512 per rule and 8 per condition of its longest set come to at most
+ * 163,776 (about 300 rules with few features, fewer than 64 with 512).  Errors:
  * AERL_ENOENT, AERL_EINVAL (also: rule sets too long for the adjoint
  * kernel), AERL_EDEVICE. */
 aerl_status aerl_soft_backward(aerl_ctx *ctx, int32_t dataset_id, int32_t pop_id,
@@ -486,8 +488,9 @@ aerl_status aerl_soft_backward(aerl_ctx *ctx, int32_t dataset_id, int32_t pop_id
  *   P_c = exp(beta * v_c) / sum_c' exp(beta * v_c'),
  * loss[s] = mean over samples of min(-log P(label), 100).  The order of the
  * rules does not matter under this head.  beta: finite, >= 0 (the
- * sharpness).  At most 16 classes.  ws: forward_bytes of
- * aerl_soft_workspace_bytes.  Deterministic.  Errors: as aerl_soft_forward,
+ * sharpness).  At most 16 classes, and 512 bytes per feature and 8 per rule set
+ * of a block (64 at most) have to fit 163,776 (318 features always do).  ws:
+ * forward_bytes of aerl_soft_workspace_bytes.  Deterministic.  Errors: as aerl_soft_forward,
  * plus AERL_EINVAL (more than 16 classes, bad beta). */
 aerl_status aerl_softmax_forward(aerl_ctx *ctx, int32_t dataset_id, int32_t pop_id,
                                  const float *coef, const float *coef2, const float *theta,
@@ -498,6 +501,8 @@ aerl_status aerl_softmax_forward(aerl_ctx *ctx, int32_t dataset_id, int32_t pop_
  * aerl_soft_backward): dL/dv_c = beta (P_c - [c = y]),
  * dL/dr_k = dL/dv_{class_k} - dL/dv_default * prod_{i != k} (1 - r_i),
  * dL/dz = dL/dr_k * r_k * sigmoid(-z).  Every sigmoid is recomputed.
+ * The bound of aerl_soft_backward holds from 17 rules on, and for any rule set
+ * with more than 64 features or four classes.
  * ws: backward_bytes.  Deterministic.  Errors: as aerl_soft_backward, plus
  * AERL_EINVAL (more than 16 classes, rule sets too long for the kernel's
  * LDS, bad beta). */

@@ -457,7 +457,7 @@ hipError_t launch_predict(const PopRec &pop, int32_t set, const float *rows, int
   const int64_t blocks = (n + kPredictRows * S - 1) / (kPredictRows * S);
   if (lds > kDynLdsMax) return hipErrorInvalidValue;
   // A wave per rule while all blocks are resident at once (latency: 4096 rows
-  // x 64 features 9.1 us).  Larger requests take fewer waves per block, whose
+  // x 64 features 9.4 us).  Larger requests take fewer waves per block, whose
   // walks end once every row is decided, but enough for 16 per CU under the
   // LDS of their rows.
   int waves = 1, least = 1;

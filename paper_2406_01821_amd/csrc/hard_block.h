@@ -12,8 +12,9 @@ namespace aerl {
 // Kernels running hard_block with 1024-thread blocks: two such blocks share a
 // CU (eight waves per SIMD) only when a wave holds at most 64 VGPRs and 80
 // SGPRs; measured on gfx950, 82 already leave room for one block.  This cap
-// and eight waves per SIMD in the launch bounds make the compiler keep within them (spilling a few loop-invariant values to VGPR lanes
-// outside the rule-set loop); the asm walk's fixed quads s[64:71] lie below it.
+// and eight waves per SIMD in the launch bounds make the compiler keep within
+// them (spilling a few loop-invariant values to VGPR lanes outside the rule-set
+// loop); the asm walk's fixed quads s[64:71] lie below it.
 #define AERL_HARD_SGPR_CAP __attribute__((amdgpu_num_sgpr(80)))
 
 typedef float f4v __attribute__((ext_vector_type(4)));
