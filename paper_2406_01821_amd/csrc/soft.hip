@@ -701,7 +701,7 @@ __device__ __forceinline__ void bwd_rule_conds(const SoftArgs &a, const float *x
 // Adjoint for rule sets of at most kRegRules rules with S samples per lane:
 // the per-rule state kept between the two sweeps is l_k = a_k + (survival
 // before k) and log2(1 - r_k), in per-lane private memory (scratch, served by
-// the vector caches: only the rows of a set's own rules are touched; R, 16 or
+// the vector caches: only the rows of a set's own rules are touched; R, 32 or
 // 64, bounds what is reserved).  The reverse sweep recomputes every
 // condition once for its sigmoid(-z); only a rule of the label adds its
 // conditions up again, for the a_k of the U recurrence (the other rules' step

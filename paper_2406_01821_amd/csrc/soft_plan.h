@@ -22,10 +22,14 @@ constexpr int kBwdWaves = 8, kSmaxBwdWaves = 4;
 constexpr int kProdMaxConds = 60;  // most conditions of a rule in product form
 // Most rules whose state the adjoints keep in private memory, and the bound of
 // the variants for shorter rule sets.  The runtime reserves a kernel's private
-// memory for every wave that the GPU can hold, whatever the population: 16 rules
-// take 520 bytes per lane (270 MB) with four samples, 64 rules 2080 (1.1 GB),
-// under the softmax head 780 and 3100.
-constexpr int kRegRules = 64, kFewRules = 16;
+// memory for every wave that the GPU can hold, whatever the population: 32 rules
+// take 1040 bytes per lane (540 MB) with four samples, 64 rules 2080 (1.1 GB),
+// under the softmax head 1560 and 3100.  A launch that asks for less than one
+// before it keeps the larger one's stride between waves, which makes it slower
+// (53,348 x 26, 135 sets of 13 rules, after sets of 24: 454 us in a variant for
+// 16 rules, 430 in this one, 420 before either): so the line is above the rules
+// that populations usually have, and not below it.
+constexpr int kRegRules = 64, kFewRules = 32;
 
 struct SoftPlan {
   int S, Q, TG, n_groups;
